@@ -1,0 +1,514 @@
+// Slot-walking neighbourhood convolution for any shape (Eqs. 4-5 with the
+// activation of Eq. 10), from a neighbour-row table or from coordinates:
+//
+//   out[i][n] = act( bias[n] + sum_kk A[i][kk] W[kk][n] ),  kk = j Cin + c,
+//   A[i][j Cin + c] = S[r_ij][c], absent rows 0,
+//
+// the slots concatenated into one reduction axis of K Cin entries, walked in
+// 64-byte k-steps (32 bf16 or 16 fp32 entries), four of them to a phase.
+//
+// A workgroup owns R = 16 RW active rows and BN = 16 CW NCT output columns;
+// its wavefronts form an RW x CW grid of 16 rows x 16 NCT columns.  Per phase:
+//   * the phase's weight rows are in one of two LDS buffers, stored by all
+//     threads one phase ahead from registers loaded NWS phases before that;
+//     one barrier per phase;
+//   * a wavefront's own input rows come straight from memory into registers,
+//     16 bytes per lane and k-step, NA - 1 phases ahead.  Raw buffer loads: an
+//     absent row gets an offset past the buffer and costs no memory access.
+//     Their offsets (an LDS read of the row's slot) are formed a phase
+//     earlier still;
+//   * the weight fragments of k-step s + 1 are read from LDS before the MFMAs
+//     of k-step s; no branch inside a phase.  A wavefront none of whose rows
+//     has a slot of the phase skips it.  Workgroups of 128 rows sort their
+//     rows by first sparse slot first, so that wavefronts share their slots.
+// The product is taken transposed (A operand: weight columns, B operand:
+// rows), so a lane ends with whole 16-byte runs of columns of one row and
+// stores them without an LDS pass.  Each output element is summed over the
+// slots in order and within a slot over the k-steps in order, as in the other
+// conv kernels: where they run the same shape the results are the same bits.
+//
+// What bounds it.  Few rows: the chain of phases, each about 0.6 us (barrier,
+// LDS write to read, a dependent MFMA chain), so 16-row workgroups spread over
+// the CUs (262 rows, K = 9, fp32 16 -> 64: 16.8 us before, in five workgroups
+// of the weight-stationary kernel, 6.9 us here; 1,965 rows 128 -> 128 fp32:
+// 96 -> 18.6 us; 1,965 rows bf16 256 -> 256: 56 -> 15.8 us).  Many rows in
+// fp32: the fp32 matrix rate (a 128-row phase takes 1.75 us of a CU, 153
+// TFLOP/s chip-wide) plus the index prologue of every workgroup (499 K rows
+// 64 -> 64 with 0.91 of the slots present: 400 -> 370 us; 32 K rows
+// 128 -> 128: 117 -> 80 us).  Many rows in bf16: the weight stage per 128 rows
+// (93 K rows, K = 5, 32 -> 80: 30 -> 26 us; 19 K rows, K = 7, 48 -> 80 from
+// coordinates: 16.2 -> 11.7 us).
+#include <mutex>
+
+#include "shc_internal.h"
+
+namespace shc {
+
+bool conv_walk_small(const GemmArgs& a, int num_cus) {
+  return ((a.n_rows + 15) / 16) * ((a.Cout + 63) / 64) <= num_cus;
+}
+
+bool conv_walk_medium(const GemmArgs& a, int num_cus, int per_cu) {
+  return ((a.n_rows + 127) / 128) * ((a.Cout + 31) / 32) <= (int64_t)per_cu * num_cus;
+}
+
+namespace {
+
+constexpr int kWalkMaxSlots = 32;
+constexpr int kWalkLdsLimit = 160 * 1024;
+constexpr int kWalkBufferWord3 = 0x00020000;  // raw buffer resource, 32-bit data
+constexpr uint32_t kWalkOutOfRange = 0x80000000u;
+constexpr int kPhaseSteps = 4;  // 64-byte k-steps per phase
+#define SHC_WALK_LDS __attribute__((address_space(3)))
+
+typedef __bf16 walk_bf16x4 __attribute__((__vector_size__(4 * sizeof(__bf16))));
+typedef __bf16 walk_bf16x2 __attribute__((ext_vector_type(2)));
+typedef float walk_f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t walk_v4u32 __attribute__((ext_vector_type(4)));
+typedef uint32_t walk_v2u32 __attribute__((ext_vector_type(2)));
+
+// weight row in LDS: fp32 rows padded by 16 bytes (the four rows a lane group
+// apart then start 16 banks apart); bf16 rows unpadded, 32-byte chunks swizzled
+__host__ __device__ constexpr int walk_wrow(bool bf16, int bn) { return bf16 ? bn * 2 : bn * 4 + 16; }
+__host__ __device__ constexpr int walk_wbuf(bool bf16, int bn) {
+  return kPhaseSteps * (bf16 ? 32 : 16) * walk_wrow(bf16, bn);
+}
+// index area (words): srcs [K][R]; sorted: srcs_in [K][R], perm [R], cnt [K],
+// hist [K + 2]; blkmask [R / 16]
+__host__ __device__ constexpr int walk_idx_bytes(int K, int R, bool sorted) {
+  return 4 * (K * R + R / 16 + (sorted ? K * R + R + 2 * K + 2 : 0));
+}
+
+// NA: register sets of input rows (NA - 1 phases in flight); NWS: register
+// sets of weights; MINW: wavefronts per SIMD that the registers must allow.
+template <bool BF16, int RW, int CW, int NCT, int NA, int NWS, int MINW>
+__global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs a) {
+  constexpr int NT = 64 * RW * CW;
+  constexpr int E = BF16 ? 2 : 4;
+  constexpr int VE = 16 / E;                 // elements per 16 bytes
+  constexpr int KSTEP = 64 / E;
+  constexpr int KC = kPhaseSteps * KSTEP;    // reduction entries per phase
+  constexpr int R = RW * 16;
+  constexpr int BN = CW * NCT * 16;
+  constexpr int WROW = walk_wrow(BF16, BN);
+  constexpr int WBUF = walk_wbuf(BF16, BN);
+  constexpr int VPR = BN * E / 16;
+  constexpr int NWV = KC * VPR / NT;         // weight vectors per thread and phase
+  static_assert(KC * VPR % NT == 0, "whole weight vectors per thread");
+  constexpr bool SORT = R >= 64;
+  // fp32: P tiles interleave their columns (entry q of tile ct is column
+  // P q + ct of the P tiles' 16 P), so one LDS read gives a lane its weights
+  // of P tiles and it ends with 4 P consecutive columns of its row
+  constexpr int P = BF16 ? 1 : (NCT < 4 ? NCT : 4);
+  typedef float WVec __attribute__((ext_vector_type(P == 1 ? 2 : P)));  // (P = 1: scalar reads)
+
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int K = a.K;
+  int32_t* srcs = reinterpret_cast<int32_t*>(smem + 2 * WBUF);        // [K][R] by position
+  uint32_t* blkmask = reinterpret_cast<uint32_t*>(srcs + K * R);      // [R / 16]
+  int32_t* srcs_in = reinterpret_cast<int32_t*>(blkmask + R / 16);    // [K][R] by row
+  int32_t* perm = srcs_in + K * R;                                    // [R] position -> row
+  int32_t* cnt = perm + R;                                            // [K]
+  int32_t* hist = cnt + K;                                            // [K + 2]
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const int wr = wave / CW;
+  const int wc = wave % CW;
+  const int g = lane >> 4;
+  const int l16 = lane & 15;
+  const int64_t n = a.n_rows;
+  const int Cin = a.Cin, Cout = a.Cout;
+  const int Ktot = K * Cin;
+  const int nks = (Ktot + KSTEP - 1) / KSTEP;
+  const int nph = (nks + kPhaseSteps - 1) / kPhaseSteps;
+  const int n0 = blockIdx.y * BN;
+
+  // workgroup b runs on XCD b % 8: each XCD takes a contiguous range of rows,
+  // so that neighbour rows of one body stay in its L2
+  const int ntiles = gridDim.x, per_xcd = ntiles / 8, rem = ntiles % 8;
+  const int xcd = blockIdx.x % 8;
+  const int tile = (xcd < rem ? xcd * (per_xcd + 1) : rem * (per_xcd + 1) + (xcd - rem) * per_xcd) +
+                   (int)(blockIdx.x / 8);
+  const int64_t row0 = (int64_t)tile * R;
+  const int nrows = (int)min((int64_t)R, n - row0);
+
+  // ---- weights of a phase: global -> registers -> LDS.  Rows past K Cin and
+  // columns past Cout read zeros (an offset past the buffer).
+  const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(a.W), (short)0, (int)((int64_t)Ktot * Cout * E), kWalkBufferWord3);
+  auto load_w = [&](int p, i32x4 (&wv)[NWV]) {
+#pragma unroll
+    for (int u = 0; u < NWV; ++u) {
+      const int v = u * NT + tid;
+      const int k = p * KC + v / VPR;
+      const int c = n0 + (v % VPR) * VE;
+      const uint32_t off = (k < Ktot && c < Cout)
+                               ? ((uint32_t)k * (uint32_t)Cout + (uint32_t)c) * E
+                               : kWalkOutOfRange;
+      wv[u] = __builtin_bit_cast(i32x4,
+                                 __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, off, 0, 0));
+    }
+  };
+  // bf16: the 32-byte column chunk c of row r sits at c ^ swz_row(r), which
+  // puts the rows a transposing read touches on different bank groups
+  auto swz_row = [](int r) -> int {
+    if constexpr (BN >= 128) return (r & 3) | (((r >> 3) & 1) << 2);
+    else if constexpr (BN >= 64) return ((r >> 1) & 1) | (((r >> 3) & 1) << 1);
+    else return ((r >> 1) ^ (r >> 3)) & 1;
+  };
+  auto store_w = [&](int buf, const i32x4 (&wv)[NWV]) {
+    unsigned char* base = smem + buf * WBUF;
+#pragma unroll
+    for (int u = 0; u < NWV; ++u) {
+      const int v = u * NT + tid;
+      const int k = v / VPR;
+      const int q = v % VPR;
+      const int col = BF16 ? (((q >> 1) ^ swz_row(k)) << 5) + ((q & 1) << 4) : q * 16;
+      *reinterpret_cast<i32x4*>(base + k * WROW + col) = wv[u];
+    }
+  };
+  i32x4 wreg[NWS][NWV];
+#pragma unroll
+  for (int s = 0; s < NWS; ++s) load_w(s, wreg[s]);
+
+  // ---- index lists ------------------------------------------------------------
+  if (tid < R / 16) blkmask[tid] = 0;
+  if constexpr (SORT) {
+    for (int q = tid; q < 2 * K + 2; q += NT) cnt[q] = 0;  // cnt and hist
+  }
+  __syncthreads();
+  const int KR = K * R;
+  int32_t* first = SORT ? srcs_in : srcs;
+  constexpr int EB = 4;  // entries per thread in flight
+  for (int e0 = 0; e0 < KR; e0 += EB * NT) {
+    int32_t s[EB];
+    bool in[EB];
+#pragma unroll
+    for (int u = 0; u < EB; ++u) in[u] = e0 + u * NT + tid < KR && (e0 + u * NT + tid) % R < nrows;
+    if (a.table != nullptr) {
+#pragma unroll
+      for (int u = 0; u < EB; ++u) {
+        const int e = in[u] ? e0 + u * NT + tid : 0;
+        s[u] = a.table[(int64_t)(e / R) * n + row0 + e % R];
+      }
+    } else {
+      int2 c[EB];
+#pragma unroll
+      for (int u = 0; u < EB; ++u)
+        c[u] = reinterpret_cast<const int2*>(a.coords)[row0 + (in[u] ? (e0 + u * NT + tid) % R : 0)];
+      int32_t nb[EB];
+#pragma unroll
+      for (int u = 0; u < EB; ++u) {
+        in[u] = in[u] && c[u].x >= 0 && c[u].x < a.B && c[u].y >= 0 && c[u].y < a.V;
+        nb[u] = a.nbr[in[u] ? (int64_t)c[u].y * K + (e0 + u * NT + tid) / R : 0];
+      }
+#pragma unroll
+      for (int u = 0; u < EB; ++u) {
+        in[u] = in[u] && nb[u] >= 0 && nb[u] < a.V;
+        s[u] = a.inv[in[u] ? (int64_t)c[u].x * a.V + nb[u] : 0];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < EB; ++u) {
+      const int e = e0 + u * NT + tid;
+      const bool ok = in[u] && s[u] >= 0 && (int64_t)s[u] < n;
+      const uint64_t bal = __ballot(ok);
+      if (e < KR) {
+        first[e] = ok ? s[u] : -1;
+        if constexpr (SORT) {
+          if (lane == 0 && bal != 0) atomicAdd(&cnt[e / R], __popcll(bal));
+        } else {
+          // 16 consecutive entries share a slot and a block
+          if (l16 == 0 && ((bal >> (lane & 48)) & 0xFFFFu) != 0) atomicOr(&blkmask[(e % R) / 16], 1u << (e / R));
+        }
+      }
+    }
+  }
+  if constexpr (SORT) {
+    __syncthreads();
+    // rows sorted by their first sparse slot (one present in fewer than half
+    // of the rows): bucket 0 has dense slots only, 1 + j first sparse slot j,
+    // K + 1 is past the last row.  The order inside a bucket is whatever the
+    // atomics give, which no result depends on.
+    constexpr int RPT = (R + NT - 1) / NT;
+    int bkt[RPT];
+    uint32_t rm[RPT];
+    uint32_t dense = 0;
+    for (int j = 0; j < K; ++j) dense |= (2 * cnt[j] >= nrows ? 1u : 0u) << j;
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      const int t = tid + i * NT;
+      rm[i] = 0;
+      bkt[i] = -1;
+      if (t < R) {
+        for (int j = 0; j < K; ++j) rm[i] |= (srcs_in[j * R + t] >= 0 ? 1u : 0u) << j;
+        const uint32_t key = rm[i] & ~dense;
+        bkt[i] = t >= nrows ? K + 1 : (key ? 1 + __builtin_ctz(key) : 0);
+        atomicAdd(&hist[bkt[i]], 1);
+      }
+    }
+    __syncthreads();
+    if (wave == 0) {  // exclusive scan of the K + 2 <= 34 counts, one per lane
+      const int c = lane < K + 2 ? hist[lane] : 0;
+      int inc = c;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(inc, d, 64);
+        if (lane >= d) inc += y;
+      }
+      if (lane < K + 2) hist[lane] = inc - c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      const int t = tid + i * NT;
+      if (t < R) {
+        const int pos = atomicAdd(&hist[bkt[i]], 1);
+        perm[pos] = t;
+        for (int j = 0; j < K; ++j) srcs[j * R + pos] = srcs_in[j * R + t];
+        if (rm[i]) atomicOr(&blkmask[pos >> 4], rm[i]);
+      }
+    }
+  }
+  store_w(0, wreg[0]);
+  load_w(NWS, wreg[0]);
+  __syncthreads();
+
+  // ---- this wavefront's blocks --------------------------------------------------
+  const uint32_t all = __builtin_amdgcn_readfirstlane(blkmask[wr]);
+  const __amdgpu_buffer_rsrc_t s_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(a.S), (short)0, (int)(n * Cin * E), kWalkBufferWord3);
+  // slot of reduction entry kk by multiply-high (exact: kk Cin < 2^32)
+  const uint32_t magic = a.cin_magic;
+  auto slot_of = [&](int kk) -> int { return (int)__umulhi((uint32_t)kk, magic); };
+  // byte offsets of this lane's vectors of phase p (LDS reads of the rows'
+  // slots), and the loads themselves, a phase apart
+  auto offsets = [&](int p, uint32_t (&off)[kPhaseSteps]) {
+    int32_t src[kPhaseSteps];
+    uint32_t c[kPhaseSteps];
+    bool in[kPhaseSteps];
+#pragma unroll
+    for (int ks = 0; ks < kPhaseSteps; ++ks) {
+      const int kk = p * KC + ks * KSTEP + g * VE;
+      in[ks] = kk < Ktot;
+      const int j = in[ks] ? slot_of(kk) : 0;
+      c[ks] = (uint32_t)(kk - j * Cin);
+      src[ks] = srcs[j * R + wr * 16 + l16];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < kPhaseSteps; ++ks)
+      off[ks] = (in[ks] && src[ks] >= 0)
+                    ? ((uint32_t)src[ks] * (uint32_t)Cin + c[ks]) * (uint32_t)E
+                    : kWalkOutOfRange;
+  };
+  auto issue_a = [&](const uint32_t (&off)[kPhaseSteps], i32x4 (&dst)[kPhaseSteps]) {
+#pragma unroll
+    for (int ks = 0; ks < kPhaseSteps; ++ks)
+      dst[ks] = __builtin_bit_cast(
+          i32x4, __builtin_amdgcn_raw_buffer_load_b128(s_rsrc, off[ks], 0, 0));
+  };
+
+  // column of accumulator entry r of tile ct: a lane's entries of P tiles are
+  // 4 P consecutive columns
+  const int cbase = n0 + wc * NCT * 16 + 4 * P * g;
+  auto col_of = [&](int ct, int r) -> int { return cbase + (ct / P) * 16 * P + P * r + ct % P; };
+  // accumulators start at the bias of their columns (row l16 of a block)
+  f32x4 acc[NCT];
+#pragma unroll
+  for (int ct = 0; ct < NCT; ++ct) {
+    f32x4 b = {0.f, 0.f, 0.f, 0.f};
+    if (a.bias != nullptr) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) b[r] = col_of(ct, r) < Cout ? a.bias[col_of(ct, r)] : 0.f;
+    }
+    acc[ct] = b;
+  }
+
+  i32x4 areg[NA][kPhaseSteps];
+  uint32_t off[kPhaseSteps];  // of the phase whose loads go out next
+#pragma unroll
+  for (int s = 0; s < NA - 1; ++s) {
+    offsets(s, off);
+    issue_a(off, areg[s]);
+  }
+  offsets(NA - 1, off);
+
+  // weight fragments of one k-step: bf16, two transposing reads per tile give
+  // lane (g, i) entries 8g .. 8g+7 of column i; fp32, entries 4g .. 4g+3
+  const int swz = swz_row(8 * g + (l16 >> 2));
+  struct WFrag {
+    i32x4 v[NCT];
+  };
+  auto read_w = [&](const unsigned char* base, int ks, WFrag& f) {
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct) {
+      if constexpr (BF16) {
+        const unsigned char* p0 = base + (ks * 32 + 8 * g + (l16 >> 2)) * WROW +
+                                  (((wc * NCT + ct) ^ swz) << 5) + 8 * (l16 & 3);
+        const walk_bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+            (SHC_WALK_LDS walk_bf16x4*)(const_cast<unsigned char*>(p0)));
+        const walk_bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+            (SHC_WALK_LDS walk_bf16x4*)(const_cast<unsigned char*>(p0 + 4 * WROW)));
+        const bf16x8 w = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        f.v[ct] = __builtin_bit_cast(i32x4, w);
+      } else if constexpr (P == 1) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          f.v[ct][i] = *reinterpret_cast<const int*>(base + (ks * 16 + 4 * g + i) * WROW +
+                                                     ((wc * NCT + ct) * 16 + l16) * 4);
+      } else if (ct % P == 0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const WVec w = *reinterpret_cast<const WVec*>(
+              base + (ks * 16 + 4 * g + i) * WROW + ((wc * NCT + ct) * 16 + P * l16) * 4);
+#pragma unroll
+          for (int q = 0; q < P; ++q) f.v[ct + q][i] = __float_as_int(w[q]);
+        }
+      }
+    }
+  };
+  auto phase = [&](int p, i32x4 (&cur)[kPhaseSteps], i32x4 (&ahead)[kPhaseSteps],
+                   i32x4 (&wv)[NWV]) {
+    // phase p's weights were stored before this barrier; every wavefront is
+    // done with phase p - 1, whose buffer takes phase p + 1's
+    __syncthreads();
+    const unsigned char* base = smem + (p & 1) * WBUF;
+    // the slots of the phase; a wavefront none of whose rows has one skips it
+    uint32_t bits = 0;
+    if (p < nph) {
+      const int lo = slot_of(p * KC), hi = slot_of(min((p + 1) * KC, Ktot) - 1);
+      bits = ((2u << hi) - 1u) & ~((1u << lo) - 1u);
+    }
+    const bool live = (all & bits) != 0u;
+    WFrag wf[2];
+    if (live) read_w(base, 0, wf[0]);
+    issue_a(off, ahead);
+    store_w((p + 1) & 1, wv);
+    load_w(p + 1 + NWS, wv);
+    offsets(p + NA, off);
+    if (!live) return;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < kPhaseSteps; ++ks) {
+      if (ks + 1 < kPhaseSteps) read_w(base, ks + 1, wf[(ks + 1) & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (BF16) {
+        const bf16x8 af = __builtin_bit_cast(bf16x8, cur[ks]);
+#pragma unroll
+        for (int ct = 0; ct < NCT; ++ct)
+          acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              __builtin_bit_cast(bf16x8, wf[ks & 1].v[ct]), af, acc[ct], 0, 0, 0);
+      } else {  // MFMA i contracts entry 4g + i of every lane group
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int ct = 0; ct < NCT; ++ct)
+            acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                __int_as_float(wf[ks & 1].v[ct][i]), __int_as_float(cur[ks][i]), acc[ct], 0, 0,
+                0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // register sets: phase p multiplies rows p % NA and stores weights
+  // (p + 1) % NWS; whole trips of U phases (phases past the end do nothing)
+  constexpr int U = NA % NWS == 0 ? NA : (NWS % NA == 0 ? NWS : NA * NWS);
+  for (int p0 = 0; p0 < nph; p0 += U) {
+#pragma unroll
+    for (int q = 0; q < U; ++q)
+      phase(p0 + q, areg[q % NA], areg[(q + NA - 1) % NA], wreg[(q + 1) % NWS]);
+  }
+
+  // ---- epilogue: activation, rounding, four columns of a row per store ---------
+  // The last MFMAs may sit right behind a branch; their results are read at
+  // least 32 wait states later (an fp32 16x16x4 needs 18).
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  const bool relu = a.relu != 0;
+  const __amdgpu_buffer_rsrc_t o_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      a.out, (short)0, (int)(n * Cout * E), kWalkBufferWord3);
+  const int pos = wr * 16 + l16;
+  const int r = SORT ? perm[pos] : pos;
+#pragma unroll
+  for (int ct = 0; ct < NCT; ++ct) {
+    // vector ct % P of the 4 P columns of tiles ct / P * P ..: entries
+    // 4 (ct % P) + i of them
+    const int c0 = ct / P * P;
+    const int col = col_of(c0, 0) + 4 * (ct % P);
+    const uint32_t off = (r < nrows && col < Cout)
+                             ? ((uint32_t)(row0 + r) * (uint32_t)Cout + (uint32_t)col) * E
+                             : kWalkOutOfRange;
+    f32x4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int q = 4 * (ct % P) + i;
+      const float x = acc[c0 + q % P][q / P];
+      const float rx = x > 0.f ? x : 0.f;
+      v[i] = relu ? rx : x;
+    }
+    if constexpr (BF16) {  // round to nearest even
+      const walk_bf16x2 h0 = __builtin_convertvector(walk_f32x2{v[0], v[1]}, walk_bf16x2);
+      const walk_bf16x2 h1 = __builtin_convertvector(walk_f32x2{v[2], v[3]}, walk_bf16x2);
+      const walk_v2u32 o = {__builtin_bit_cast(uint32_t, h0), __builtin_bit_cast(uint32_t, h1)};
+      __builtin_amdgcn_raw_buffer_store_b64(o, o_rsrc, off, 0, 0);
+    } else {
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(walk_v4u32, v), o_rsrc, off, 0,
+                                             0);
+    }
+  }
+}
+
+template <bool BF16, int RW, int CW, int NCT, int NA, int NWS, int MINW>
+hipError_t launch_walk(const GemmArgs& a, hipStream_t stream) {
+  constexpr int R = RW * 16, BN = CW * NCT * 16;
+  auto kern = conv_walk_kernel<BF16, RW, CW, NCT, NA, NWS, MINW>;
+  static std::once_flag once;
+  static hipError_t attr_err = hipSuccess;
+  std::call_once(once, [&] {
+    attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, kWalkLdsLimit);
+  });
+  if (attr_err != hipSuccess) return attr_err;
+  const size_t lds =
+      2 * walk_wbuf(BF16, BN) + walk_idx_bytes(a.K, R, R >= 64);
+  const dim3 grid((unsigned)((a.n_rows + R - 1) / R), (unsigned)((a.Cout + BN - 1) / BN));
+  hipLaunchKernelGGL(kern, grid, dim3(64 * RW * CW), lds, stream, a);
+  return hipGetLastError();
+}
+
+// Workgroups of 16 rows x 64 columns while the chip holds them at once, else
+// 128 x 32 while two to a CU hold them, else 128 x 64: fp32 64 -> 64 at 3,930
+// rows 12.4 / 16.3 / 23.9 us, at 7,926 rows 17.4 / 17.0 / 24.2; 128 -> 128 at
+// 15,851 rows (992 workgroups of 128 x 32) 96 / 41.6 / 42.1, at 32,000 rows
+// 183 / 90 / 80; bf16 256 -> 256 at 7,926 rows 71 / 24.8 / 20.5.
+template <bool BF16>
+hipError_t launch_walk_rows(const GemmArgs& a, int num_cus, hipStream_t stream) {
+  if (conv_walk_small(a, num_cus))
+    return launch_walk<BF16, 1, 4, 1, 4, 4, 1>(a, stream);
+  if (conv_walk_medium(a, num_cus, 2)) return launch_walk<BF16, 8, 1, 2, 2, 2, 4>(a, stream);
+  return launch_walk<BF16, 8, 1, 4, 2, 1, 4>(a, stream);
+}
+
+}  // namespace
+
+bool conv_walk_supported(const GemmArgs& a, bool bf16) {
+  const int e = bf16 ? 2 : 4;
+  if (a.plan != nullptr || a.plan_out != nullptr) return false;
+  if (a.K < 1 || a.K > kWalkMaxSlots) return false;
+  // 32-bit buffer offsets
+  return a.n_rows * a.Cin * e <= 0x7FFF0000LL && a.n_rows * a.Cout * e <= 0x7FFF0000LL &&
+         (int64_t)a.K * a.Cin * a.Cout * e <= 0x7FFF0000LL;
+}
+
+hipError_t launch_conv_walk(const GemmArgs& a_in, bool bf16, int num_cus, hipStream_t stream) {
+  GemmArgs a = a_in;
+  a.cin_magic = (uint32_t)(((1ull << 32) + (uint64_t)a.Cin - 1) / (uint64_t)a.Cin);
+  return bf16 ? launch_walk_rows<true>(a, num_cus, stream)
+              : launch_walk_rows<false>(a, num_cus, stream);
+}
+
+}  // namespace shc

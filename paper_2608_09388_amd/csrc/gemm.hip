@@ -633,13 +633,35 @@ hipError_t launch_gather_gemm(const GemmArgs& a, bool conv, bool bf16, hipStream
   // channels within one round of 128-row groups (6.6 against 10.6 us at
   // 4,200 rows); slower for 128 input channels at a few hundred rows per CU
   // (36 against 26 us at 5% of the density-sweep batch).
+  // The slot-walking conv (conv_walk.hip) against both, the same bits:
+  //   * bf16 64 -> 128 channels: 8.8 / 8.7 / 9.0 us at 2,000 / 4,000 / 8,000
+  //     rows against 9.6 / 9.9 / 9.9 for the slot-major kernel, while its 128 x
+  //     32 workgroups fit one to a CU;
+  //   * fp32: 6.9 against 16.8 us (262 rows, 16 -> 64), 12.4 against 14.5
+  //     (3,930 rows, 64 -> 64), 18.6 against 96 (1,965 rows, 128 -> 128, where
+  //     W leaves no column slice and the tiled kernel ran) while its 16-row
+  //     workgroups run at once; past that the weight-stationary kernel is
+  //     faster at 64 input channels (17.1 against 14.9 us at 7,926 rows) and
+  //     slower at few reduction entries (16 channels, 15,851 rows: 10.4
+  //     against 19.2 us; 32 channels: 12.3 against 14.6), up to 32 a slot at
+  //     K = 9;
+  //   * everything the weight-stationary kernel does not take.
+  const bool walk = conv && conv_walk_supported(a, bf16);
+  if (walk && bf16 && a.Cin == 64 && a.Cout == 128 && conv_sm_supported(a, bf16) &&
+      conv_walk_medium(a, cus, 1))
+    return launch_conv_walk(a, bf16, cus, stream);
   if (conv && conv_sm_supported(a, bf16) &&
       (a.n_rows >= 1000LL * cus || (a.Cin == 64 && a.n_rows <= 128LL * cus)))
     return launch_conv_sm(a, cus, stream);
+  if (walk && !bf16 &&
+      (conv_walk_small(a, cus) || (a.K * a.Cin <= 288 && conv_walk_medium(a, cus, 2))))
+    return launch_conv_walk(a, bf16, cus, stream);
   WsPlan plan;
   if (ws_plan(a, conv, bf16, cus, &plan)) return launch_ws_gemm(a, conv, bf16, plan, stream);
   // a conv plan exists only for the weight-stationary kernel
   if (a.plan != nullptr || a.plan_out != nullptr) return hipErrorInvalidValue;
+  if (walk) return launch_conv_walk(a, bf16, cus, stream);
+  // the linear layer, and convs whose buffers need 64-bit offsets
   if (bf16) return conv ? launch_typed<true, true>(a, stream) : launch_typed<true, false>(a, stream);
   return conv ? launch_typed<false, true>(a, stream) : launch_typed<false, false>(a, stream);
 }

@@ -176,6 +176,13 @@ int64_t conv_plan_max_rows(const GemmArgs& a, bool bf16, int num_cus);
 int64_t conv_plan_bytes_upto(const GemmArgs& a, bool bf16, int num_cus);
 hipError_t launch_ws_gemm(const GemmArgs& a, bool conv, bool bf16, const WsPlan& plan,
                           hipStream_t stream);
+// slot-walking conv for any shape whose buffers stay below 2 GiB
+// (conv_walk.hip), and whether its smallest workgroups (16 rows x 64 columns)
+// all run at once, or its middle ones (128 x 32) at per_cu to a CU
+bool conv_walk_supported(const GemmArgs& a, bool bf16);
+bool conv_walk_small(const GemmArgs& a, int num_cus);
+bool conv_walk_medium(const GemmArgs& a, int num_cus, int per_cu);
+hipError_t launch_conv_walk(const GemmArgs& a, bool bf16, int num_cus, hipStream_t stream);
 // slot-major conv from a neighbour-row table (conv_sm.hip): bf16, C_in and
 // C_out in {64, 128}, K <= 32, no plan
 bool conv_sm_supported(const GemmArgs& a, bool bf16);

@@ -1,0 +1,76 @@
+"""The sparse neighbour conv on the shapes its slot-walking kernel serves:
+small active sets and channel counts the other conv kernels do not take, at
+the edges of its 16- and 128-row workgroups, 32- and 64-column slices and
+256-byte reduction phases (phases that hold several slots, k-steps that cross
+a slot, a partial last phase), from a table and from coordinates (the same
+bits), with and without bias and ReLU, against the oracle (Eqs. 4-5).  Every
+input is seeded and synthetic.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import shc_oracle as O
+from paper_2608_09388_amd import binding as shc
+from paper_2608_09388_amd import synth
+from tests.gpu_util import TORCH, Compaction, assert_scaled_close, down, require_gpu, up
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    return require_gpu()
+
+
+@pytest.mark.parametrize("dtype,B,V,n,K,Cin,Cout", [
+    ("f32", 1, 40, 1, 9, 16, 64),          # one row
+    ("f32", 2, 60, 17, 9, 16, 16),         # a second block of one row, 4 slots a phase
+    ("f32", 4, 655, 262, 9, 16, 64),       # the tiny layer
+    ("f32", 3, 500, 129, 5, 48, 80),       # partial columns, phases across slots
+    ("f32", 3, 900, 255, 9, 192, 64),      # three phases a slot
+    ("f32", 6, 700, 1000, 32, 32, 48),     # 32 slots
+    ("f32", 40, 655, 9000, 9, 16, 64),     # 128 x 32 workgroups, a ragged last one
+    ("f32", 30, 655, 8321, 3, 144, 144),   # 128 x 32, K Cin past a phase
+    ("f32", 40, 655, 20000, 9, 64, 128),   # 128 x 64, dense slots
+    ("bf16", 1, 40, 15, 9, 16, 16),        # a k-step over two slots
+    ("bf16", 3, 500, 128, 7, 48, 80),      # k-steps that cross slots
+    ("bf16", 5, 655, 1000, 9, 64, 128),    # the encoder's widening layer
+    ("bf16", 5, 655, 400, 9, 256, 256),    # 256 channels
+    ("bf16", 4, 400, 700, 20, 80, 32),     # 20 slots, an odd multiple of 16
+    ("bf16", 37, 1723, 19125, 7, 48, 80),  # 128 x 32
+    ("bf16", 60, 655, 30001, 5, 32, 80),   # 128 x 64
+])
+def test_conv_walk_against_oracle(dev, dtype, B, V, n, K, Cin, Cout):
+    rng = np.random.default_rng(B + V + 7 * n + 31 * K + Cin + Cout)
+    nbr = rng.integers(-2, V + 2, size=(V, K)).astype(np.int32)   # some out of range: absent
+    nbr[:, 0] = np.arange(V)
+    m = np.zeros(B * V, dtype=np.uint8)
+    m[rng.permutation(B * V)[:n]] = 1
+    m = m.reshape(B, V)
+    c = Compaction(m)
+    assert c.run() == n
+    S = synth.as_dtype(rng.standard_normal((n, Cin)).astype(np.float32), dtype)[1]
+    W = synth.as_dtype((rng.standard_normal((K, Cin, Cout)) / np.sqrt(K * Cin))
+                       .astype(np.float32), dtype)[1]
+    bias = rng.standard_normal(Cout).astype(np.float32)
+    coords, _, _, _ = O.compact(m)
+    rows = np.unique(np.concatenate([np.arange(min(n, 150)), np.arange(max(0, n - 150), n),
+                                     rng.choice(n, size=min(n, 300), replace=False)]))
+    Sd, Wd, nd = up(S, dtype), up(W, dtype), up(nbr)
+    table = torch.full((K * n,), -7, dtype=torch.int32, device=dev)
+    shc.build_neighbor_table(c.coords, c.inv, n, B, V, nd, table)
+    oob = np.where((nbr < 0) | (nbr >= V), -1, nbr)
+    for b, act in ((bias, shc.SHC_ACT_RELU), (None, shc.SHC_ACT_NONE)):
+        bd = None if b is None else up(b)
+        out = torch.full((n + 3, Cout), float("nan"), dtype=TORCH[dtype], device=dev)
+        direct = torch.full_like(out, float("nan"))
+        shc.sparse_neighbor_conv_table(Sd, table, n, Wd, bd, out, act)
+        shc.sparse_neighbor_conv(Sd, c.coords, c.inv, n, B, V, nd, Wd, bd, direct, act)
+        got = down(out)
+        assert np.all(np.isnan(got[n:])) and np.all(np.isnan(down(direct)[n:]))
+        assert torch.equal(out[:n], direct[:n])
+        ref = O.conv_at(S, coords, B, V, oob, W, rows, b, act=act == shc.SHC_ACT_RELU)
+        scale = O.conv_at(S, coords, B, V, oob, W, rows, b, scale=True)
+        assert_scaled_close(got[rows], ref, scale, dtype,
+                            f"conv n={n} K={K} {Cin}->{Cout} act={act}", n_terms=K * Cin)
