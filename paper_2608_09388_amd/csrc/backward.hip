@@ -293,16 +293,8 @@ __global__ __launch_bounds__(kThreads) void tt_kernel(const int2* __restrict__ c
 }
 
 // ---------------------------------------------------------------------------
-// wgrad: presence mask, chunk schedule, partial tiles, reduction
+// wgrad: chunk schedule, partial tiles, reduction
 // ---------------------------------------------------------------------------
-
-__global__ __launch_bounds__(kThreads) void presence_kernel(const int32_t* __restrict__ table,
-                                                            int64_t total,
-                                                            uint8_t* __restrict__ m) {
-  for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * kThreads)
-    m[e] = table[e] >= 0 ? 1 : 0;
-}
 
 // chunks of L rows of slot j's list: the first one's index and the count
 __device__ inline void slot_chunks(const int32_t* __restrict__ row_ptr, int j, int32_t L,
@@ -1402,26 +1394,16 @@ size_t slot_pairs_ws_bytes(int64_t n, int32_t K) {
   int64_t per_block = 0;
   const int64_t kn = (int64_t)K * n;
   if (kn > 0) compact_plan(kn, &nb, &per_block);
-  return align256((size_t)kn) + align256((size_t)kn * 4) + align256(16) + align256((size_t)nb * 4);
+  return align256(16) + align256((size_t)nb * 4);
 }
 
 // Pair lists of an active set: (slot j, row i) for every table[j][i] >= 0,
-// slot-major with rows ascending (a compaction of the [K][n] presence
-// mask), and the slot offsets pair_ptr[K + 1].  ws: slot_pairs_ws_bytes.
+// slot-major with rows ascending (a compaction of the table's present
+// entries), and the slot offsets pair_ptr[K + 1].  ws: slot_pairs_ws_bytes.
 hipError_t launch_slot_pairs(const int32_t* table, int64_t n, int32_t K, int32_t* pairs,
                              int32_t* pair_ptr, void* ws, hipStream_t stream) {
-  unsigned char* w = static_cast<unsigned char*>(ws);
-  const int64_t kn = (int64_t)K * n;
-  uint8_t* mask = w;
-  int32_t* inv_p = reinterpret_cast<int32_t*>(w + align256((size_t)kn));
-  int32_t* nact = reinterpret_cast<int32_t*>(w + align256((size_t)kn) + align256((size_t)kn * 4));
-  int32_t* bc = nact + 64;
-  hipLaunchKernelGGL(presence_kernel, dim3(std::min<unsigned>(grid_for(kn), 8192)), dim3(kThreads),
-                     0, stream, table, kn, mask);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  return launch_compact(mask, K, (int32_t)n, pairs, inv_p, pair_ptr, nact, nullptr, kn, bc,
-                        stream);
+  int32_t* count = static_cast<int32_t*>(ws);
+  return launch_compact_present(table, K, (int32_t)n, pairs, pair_ptr, count, count + 64, stream);
 }
 
 hipError_t launch_layer_backward(int conv, const void* S, const int32_t* table,

@@ -19,6 +19,15 @@
 // block per body numbers the body's rows and keeps that numbering in LDS, so
 // the table entries of its rows -- whose neighbours lie in the same body --
 // come from LDS rather than from a second pass over `inv`.
+//
+// A mask of at most kOneLaunchBytes skips the count launch: every block counts
+// the bytes before its span itself (block 0 all of them).  At these sizes the
+// chain of launches is the cost, not the bytes: the count launch and the gap
+// behind it stood between the call and N' reaching the host.
+//
+// The slot pair lists of the backward pass are the same compaction with a
+// neighbour-row table as its mask (entry e active when table[e] >= 0), read
+// as it is rather than through a byte mask made from it.
 // Integer work only: the result is the same on every run.
 #include <mutex>
 
@@ -61,25 +70,83 @@ __device__ __forceinline__ uint32_t block_sum(uint32_t x, uint32_t* red) {
   return t;
 }
 
-// Four 4-byte groups of the chunk starting at `c0` owned by this thread; bytes
-// at or past `end` read as zero.
-__device__ __forceinline__ void load_groups(const uint8_t* mask, int64_t c0, int64_t end,
-                                            uint32_t w[4]) {
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int64_t e = c0 + (int64_t)k * kSub + (int64_t)threadIdx.x * 4;
+// Entries e .. e+3 of the flattened mask as four bytes, 0 at or past `end`
+// (e a multiple of 4): the mask's own bytes, or 1 where a table entry is a row.
+template <typename M>
+__device__ __forceinline__ uint32_t load_four(const M* mask, int64_t e, int64_t end) {
+  uint32_t v = 0;
+  if constexpr (sizeof(M) == 1) {
+    if (e + 4 <= end) return *reinterpret_cast<const uint32_t*>(mask + e);
+    for (int q = 0; q < 4; ++q)
+      if (e + q < end) v |= (uint32_t)mask[e + q] << (8 * q);
+  } else {
     if (e + 4 <= end) {
-      w[k] = *reinterpret_cast<const uint32_t*>(mask + e);
+      const i32x4 t = *reinterpret_cast<const i32x4*>(mask + e);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v |= (t[q] >= 0 ? 1u : 0u) << (8 * q);
     } else {
-      uint32_t v = 0;
       for (int q = 0; q < 4; ++q)
-        if (e + q < end) v |= (uint32_t)mask[e + q] << (8 * q);
-      w[k] = v;
+        if (e + q < end) v |= (mask[e + q] >= 0 ? 1u : 0u) << (8 * q);
     }
   }
+  return v;
 }
 
-__global__ __launch_bounds__(kThreads) void compact_count_kernel(const uint8_t* __restrict__ mask,
+// Four 4-entry groups of the chunk starting at `c0` owned by this thread.
+template <typename M>
+__device__ __forceinline__ void load_groups(const M* mask, int64_t c0, int64_t end,
+                                            uint32_t w[4]) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    w[k] = load_four(mask, c0 + (int64_t)k * kSub + (int64_t)threadIdx.x * 4, end);
+}
+
+// This thread's share of the active entries of [0, upto) and of [0, total),
+// read 16 bytes a load by T threads with eight loads in flight each.
+template <int T, typename M>
+__device__ __forceinline__ void count_share(const M* mask, int64_t upto, int64_t total,
+                                            uint32_t* before, uint32_t* all) {
+  constexpr int PER = 16 / (int)sizeof(M);
+  const int64_t nvec = total / PER;
+  uint32_t lo = 0, cnt = 0;
+  auto take = [&](int64_t e, uint32_t four) {  // entries e .. e+3 as four bytes
+    const uint32_t nz = nonzero_bytes(four);
+    const int64_t d = upto - e;
+    const uint32_t keep = d >= 4 ? 0x80808080u : (d <= 0 ? 0u : (1u << (8 * (int)d)) - 1u);
+    cnt += (uint32_t)__popc(nz);
+    lo += (uint32_t)__popc(nz & keep);
+  };
+  for (int64_t v0 = 0; v0 < nvec; v0 += 8 * T) {
+    i32x4 w[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int64_t v = v0 + k * T + threadIdx.x;
+      w[k] = reinterpret_cast<const i32x4*>(mask)[v < nvec ? v : 0];
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int64_t v = v0 + k * T + threadIdx.x;
+      if (v < nvec) {
+        if constexpr (sizeof(M) == 1) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) take(v * 16 + 4 * q, (uint32_t)w[k][q]);
+        } else {
+          uint32_t f = 0;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) f |= (w[k][q] >= 0 ? 1u : 0u) << (8 * q);
+          take(v * 4, f);
+        }
+      }
+    }
+  }
+  const int64_t e = nvec * PER + threadIdx.x;  // the last entries, one each
+  if (e < total) take(e, (sizeof(M) == 1 ? mask[e] != 0 : mask[e] >= 0) ? 1u : 0u);
+  *before = lo;
+  *all = cnt;
+}
+
+template <typename M>
+__global__ __launch_bounds__(kThreads) void compact_count_kernel(const M* __restrict__ mask,
                                                                  int64_t total, int64_t per_block,
                                                                  int32_t* __restrict__ counts) {
   __shared__ uint32_t red[kWaves];
@@ -96,8 +163,10 @@ __global__ __launch_bounds__(kThreads) void compact_count_kernel(const uint8_t* 
   if (threadIdx.x == 0) counts[blockIdx.x] = (int32_t)cnt;
 }
 
+// counts: the count kernel's, or null (every block counts for itself)
+template <typename M>
 __global__ __launch_bounds__(kThreads) void compact_write_kernel(
-    const uint8_t* __restrict__ mask, int64_t total, int64_t per_block, int32_t B, int32_t V,
+    const M* __restrict__ mask, int64_t total, int64_t per_block, int32_t B, int32_t V,
     const int32_t* __restrict__ counts, int32_t* __restrict__ coords, int32_t* __restrict__ inv,
     int32_t* __restrict__ row_ptr, int32_t* __restrict__ n_active, int64_t* n_host, int64_t cap) {
   __shared__ uint32_t red[kWaves];
@@ -115,7 +184,12 @@ __global__ __launch_bounds__(kThreads) void compact_write_kernel(
   // rows taken by the blocks before this one (block 0: by every block, N')
   const int upto = blockIdx.x == 0 ? (int)gridDim.x : (int)blockIdx.x;
   uint32_t before = 0;
-  for (int q = tid; q < upto; q += kThreads) before += (uint32_t)counts[q];
+  if (counts != nullptr) {
+    for (int q = tid; q < upto; q += kThreads) before += (uint32_t)counts[q];
+  } else {
+    uint32_t all;
+    count_share<kThreads>(mask, total, blockIdx.x == 0 ? total : start, &before, &all);
+  }
   int64_t base = block_sum(before, red);
   if (blockIdx.x == 0) {
     if (tid == 0) {
@@ -184,7 +258,8 @@ __global__ __launch_bounds__(kThreads) void compact_write_kernel(
             ++b;
           }
         }
-        if (e0 + 4 <= end) {
+        if (inv == nullptr) {  // the pair lists have no use for it
+        } else if (e0 + 4 <= end) {
           *reinterpret_cast<i32x4*>(inv + e0) = i32x4{out[0], out[1], out[2], out[3]};
         } else {
           for (int q = 0; q < 4; ++q)
@@ -298,7 +373,8 @@ __device__ __forceinline__ uint32_t in_body_bits(int32_t vs, int32_t V) {
 //   1. its first row is the count of every span of the count kernel before
 //      the span holding the body's first entry, plus the active bytes of
 //      that span up to the entry; N' is the sum over every span (block 0
-//      publishes it, as compact_write_kernel does, before anything else);
+//      publishes it, as compact_write_kernel does, before anything else).
+//      Without the count kernel (counts null) it counts the mask itself;
 //   2. the 16-byte mask groups touching the body, T per pass, one per
 //      thread: a block scan of the per-group counts numbers the body's rows;
 //      inv and row_ptr[b] are written, and LDS keeps the local row of every
@@ -341,24 +417,16 @@ __global__ __launch_bounds__(T) void compact_table_kernel(
   // 1. first row of the body, and N'
   const int64_t s0 = e0 / per_block;
   uint32_t before = 0, all = 0, part = 0;
-  for (int q = tid; q < nblocks; q += T) {
-    const uint32_t c = (uint32_t)counts[q];
-    all += c;
-    before += q < s0 ? c : 0u;
-  }
-  for (int64_t p = s0 * per_block + 4 * (int64_t)tid; p < e0; p += 4 * (int64_t)T) {
-    uint32_t w = 0;
-    if (p + 4 <= total_e) {
-      w = *reinterpret_cast<const uint32_t*>(mask + p);
-    } else {
-      for (int q = 0; q < 4; ++q)
-        if (p + q < total_e) w |= (uint32_t)mask[p + q] << (8 * q);
+  if (counts != nullptr) {
+    for (int q = tid; q < nblocks; q += T) {
+      const uint32_t c = (uint32_t)counts[q];
+      all += c;
+      before += q < s0 ? c : 0u;
     }
-    uint32_t keep = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (p + q < e0) keep |= 0x80u << (8 * q);
-    part += (uint32_t)__popc(nonzero_bytes(w) & keep);
+    for (int64_t p = s0 * per_block + 4 * (int64_t)tid; p < e0; p += 4 * (int64_t)T)
+      part += (uint32_t)__popc(nonzero_bytes(load_four(mask, p, e0)));
+  } else {
+    count_share<T>(mask, e0, total_e, &before, &all);
   }
   block_sum3<T>(before, all, part, red);
   const int64_t base = (int64_t)before + part;
@@ -460,22 +528,46 @@ void compact_plan(int64_t total, int32_t* nblocks, int64_t* per_block) {
   if (*nblocks < 1) *nblocks = 1;
 }
 
-hipError_t launch_compact(const uint8_t* mask, int32_t B, int32_t V, int32_t* coords, int32_t* inv,
-                          int32_t* row_ptr, int32_t* n_active, int64_t* n_host, int64_t cap,
-                          int32_t* block_counts, hipStream_t stream) {
+// Largest mask (in bytes read) whose blocks count for themselves: 16 loads a
+// thread of a 256-thread block, two rounds of memory latency.
+constexpr int64_t kOneLaunchBytes = 64 * 1024;
+
+template <typename M>
+static hipError_t launch_compact_of(const M* mask, int32_t B, int32_t V, int32_t* coords,
+                                    int32_t* inv, int32_t* row_ptr, int32_t* n_active,
+                                    int64_t* n_host, int64_t cap, int32_t* block_counts,
+                                    hipStream_t stream) {
   const int64_t total = (int64_t)B * V;
   int32_t nblocks;
   int64_t per_block;
   compact_plan(total, &nblocks, &per_block);
-  hipLaunchKernelGGL(compact_count_kernel, dim3(nblocks), dim3(kThreads), 0, stream, mask, total,
-                     per_block, block_counts);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(compact_write_kernel, dim3(nblocks), dim3(kThreads), 0, stream, mask, total,
-                     per_block, B, V, block_counts, coords, inv, row_ptr, n_active, n_host, cap);
+  if (total * (int64_t)sizeof(M) > kOneLaunchBytes) {
+    hipLaunchKernelGGL(compact_count_kernel<M>, dim3(nblocks), dim3(kThreads), 0, stream, mask,
+                       total, per_block, block_counts);
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+  } else {
+    block_counts = nullptr;
+  }
+  hipLaunchKernelGGL(compact_write_kernel<M>, dim3(nblocks), dim3(kThreads), 0, stream, mask,
+                     total, per_block, B, V, block_counts, coords, inv, row_ptr, n_active, n_host,
+                     cap);
   return hipGetLastError();
 }
 
+hipError_t launch_compact(const uint8_t* mask, int32_t B, int32_t V, int32_t* coords, int32_t* inv,
+                          int32_t* row_ptr, int32_t* n_active, int64_t* n_host, int64_t cap,
+                          int32_t* block_counts, hipStream_t stream) {
+  return launch_compact_of(mask, B, V, coords, inv, row_ptr, n_active, n_host, cap, block_counts,
+                           stream);
+}
+
+hipError_t launch_compact_present(const int32_t* table, int32_t K, int32_t n, int32_t* pairs,
+                                  int32_t* pair_ptr, int32_t* count, int32_t* block_counts,
+                                  hipStream_t stream) {
+  return launch_compact_of(table, K, n, pairs, nullptr, pair_ptr, count, nullptr, (int64_t)K * n,
+                           block_counts, stream);
+}
 
 bool compact_table_supported(int32_t V, int32_t K) {
   return V > 0 && V <= kCompactTableMaxV && K > 0 && K <= 32;
@@ -513,10 +605,14 @@ hipError_t launch_compact_table(const uint8_t* mask, int32_t B, int32_t V, int32
   int32_t nblocks;
   int64_t per_block;
   compact_plan(total, &nblocks, &per_block);
-  hipLaunchKernelGGL(compact_count_kernel, dim3(nblocks), dim3(kThreads), 0, stream, mask, total,
-                     per_block, block_counts);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
+  if (total > kOneLaunchBytes) {
+    hipLaunchKernelGGL(compact_count_kernel<uint8_t>, dim3(nblocks), dim3(kThreads), 0, stream,
+                       mask, total, per_block, block_counts);
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+  } else {
+    block_counts = nullptr;
+  }
   // one 16-byte group per thread and pass: 1024 threads cover 16 K vertices
   const bool big = V > 4096;
 #define SHC_CT_ARGS                                                                          \

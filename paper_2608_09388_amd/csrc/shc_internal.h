@@ -51,6 +51,12 @@ hipError_t launch_compact(const uint8_t* mask, int32_t B, int32_t V, int32_t* co
                           int32_t* row_ptr, int32_t* n_active, int64_t* n_host, int64_t cap,
                           int32_t* block_counts, hipStream_t stream);
 
+// the same over a table [K][n] of rows, entry active when >= 0: pairs (slot,
+// row) in order, pair_ptr [K + 1]
+hipError_t launch_compact_present(const int32_t* table, int32_t K, int32_t n, int32_t* pairs,
+                                  int32_t* pair_ptr, int32_t* count, int32_t* block_counts,
+                                  hipStream_t stream);
+
 // compaction that also writes the neighbour-row table of the active set
 // (table[j * N' + i], as launch_neighbor_table), one block per body: the body's
 // row numbering lives in LDS, 8 bytes per vertex

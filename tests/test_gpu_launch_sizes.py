@@ -12,7 +12,7 @@ import torch
 from oracle import shc_oracle as O
 from paper_2608_09388_amd import binding as shc
 from paper_2608_09388_amd import synth
-from tests.gpu_util import (TORCH, assert_gn_close, down, gn_floor, require_gpu, up)
+from tests.gpu_util import (TORCH, Compaction, assert_gn_close, down, gn_floor, require_gpu, up)
 
 pytestmark = pytest.mark.gpu
 
@@ -20,6 +20,67 @@ pytestmark = pytest.mark.gpu
 @pytest.fixture(scope="module")
 def dev():
     return require_gpu()
+
+
+def table_of(m, nbr):
+    B, V = m.shape
+    coords, inv, _, n = O.compact(m)
+    t = np.full((nbr.shape[1], n), -1, np.int64)
+    for j in range(nbr.shape[1]):
+        u = nbr[coords[:, 1], j].astype(np.int64)
+        ok = (u >= 0) & (u < V)
+        r = inv[coords[:, 0] * V + np.where(ok, u, 0)]
+        t[j] = np.where(ok, r, -1)
+    return t
+
+
+# the one-launch limit is 64 KB of mask: totals at and one past it, totals
+# that leave 1 to 15 bytes past a 16-byte group, bodies that start at any byte
+@pytest.mark.parametrize("B,V,p", [(1, 1, 1.0), (3, 5, 0.5), (4, 655, 0.1), (1, 65535, 0.3),
+                                   (1, 65536, 0.3), (1, 65537, 0.3), (16, 4096, 1.0),
+                                   (5, 13107, 0.05), (13, 5041, 0.0), (13, 5042, 0.2),
+                                   (100, 655, 0.4), (101, 655, 0.4)])
+def test_compaction_launches(dev, B, V, p):
+    rng = np.random.default_rng(B * 977 + V)
+    m = (rng.random((B, V)) < p).astype(np.uint8)
+    m[m != 0] = rng.integers(1, 256, size=int(m.sum()))
+    ref_c, ref_inv, ref_rp, ref_n = O.compact(m)
+    c = Compaction(m)
+    c.ws.fill_(0xAB)
+    assert c.run() == ref_n
+    assert np.array_equal(down(c.inv), ref_inv) and np.array_equal(down(c.row_ptr), ref_rp)
+    assert np.array_equal(down(c.coords)[:ref_n], ref_c)
+    if V > shc.COMPACT_TABLE_MAX_V:
+        return
+    K = 3
+    nbr = rng.integers(-1, V + 1, size=(V, K)).astype(np.int32)
+    nbr[:, 0] = np.arange(V)
+    c = Compaction(m)
+    table = torch.full((K * max(c.cap, 1),), -7, dtype=torch.int32, device=dev)
+    pc = shc.PreparedCompact(c.mask, B, V, c.coords, c.inv, c.row_ptr, c.n_dev, c.ws,
+                             nbr=up(nbr), table=table)
+    pc.start()
+    n = pc.wait()
+    torch.cuda.synchronize()
+    assert n == ref_n
+    assert np.array_equal(down(c.inv), ref_inv) and np.array_equal(down(c.row_ptr), ref_rp)
+    assert np.array_equal(down(c.coords)[:n], ref_c)
+    assert np.array_equal(down(table)[: K * n].reshape(K, n), table_of(m, nbr))
+
+
+@pytest.mark.parametrize("K,n", [(1, 1), (3, 5), (9, 1820), (9, 1821), (1, 16384), (1, 16385),
+                                 (32, 700)])
+def test_slot_pairs_launches(dev, K, n):
+    rng = np.random.default_rng(K * 31 + n)
+    t = rng.integers(0, n, size=(K, n)).astype(np.int32)
+    t[rng.random((K, n)) < 0.6] = -1
+    pairs = torch.full((K * n, 2), -7, dtype=torch.int32, device=dev)
+    ptr = torch.full((K + 1,), -7, dtype=torch.int32, device=dev)
+    shc.build_slot_pairs(up(t), n, K, pairs, ptr)
+    j, i = np.nonzero(t >= 0)
+    got = down(pairs)
+    assert np.array_equal(got[: len(j)], np.stack([j, i], 1)) and np.all(got[len(j):] == -7)
+    assert np.array_equal(down(ptr), np.concatenate([[0], np.cumsum((t >= 0).sum(1))]))
 
 
 # B above the CU count: workgroups of 256, 512 or 1024 threads by the mean row
