@@ -248,48 +248,54 @@ __global__ __launch_bounds__(kThreads) void tv_sort_kernel(const int32_t* __rest
 // ---------------------------------------------------------------------------
 
 // table_t[s * n + i] = inv[b_i * V + tv[v_i * Kt + s]] or -1; row_slots[i] has
-// bit s set when that entry is a row.  Four lanes per row, lane q taking the
-// virtual slots 16 q .. 16 q + 15 (both load rounds of all four in flight at
-// once); the row's mask is or-ed over the four lanes by shuffles.
+// bit s set when that entry is a row.  A block takes 64 rows, a wavefront 16 of
+// them with one lane per virtual slot: a row's list is one contiguous load
+// (the lists of a k-NN mesh hold 9 senders in 56 virtual slots, so most lanes'
+// inverse-map loads go to one shared address), its mask one ballot.  Both
+// rounds of loads of the 16 rows are in flight at once; the entries pass
+// through LDS so that slot s of 64 consecutive rows is one 256-byte store.
+// Bound by the slot-major table's bytes (15 MB at 67 K rows): four lanes per
+// row with 16 slots each took 17.5 us there, this 13.0 us.
+constexpr int kTtRows = 64;
 __global__ __launch_bounds__(kThreads) void tt_kernel(const int2* __restrict__ coords,
                                                       const int32_t* __restrict__ inv, int64_t n,
                                                       int32_t B, int32_t V,
                                                       const int32_t* __restrict__ tv, int32_t Kt,
                                                       int32_t* __restrict__ table_t,
                                                       uint64_t* __restrict__ row_slots) {
-  const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  const int64_t i = gid >> 2;
-  const int q = (int)(gid & 3);
-  const bool in = i < n;
-  const int2 c = coords[in ? i : 0];
-  const bool ok = in && c.x >= 0 && c.x < B && c.y >= 0 && c.y < V;
-  const int32_t* trow = tv + (int64_t)(ok ? c.y : 0) * Kt;
-  const int32_t* irow = inv + (int64_t)(ok ? c.x : 0) * V;
-  const int s0 = q * 16;
-  int32_t v[16], r[16];
+  constexpr int kWaves = kThreads / 64, RPW = kTtRows / kWaves;
+  __shared__ int32_t tile[kMaxVirtualSlots][kTtRows + 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t row0 = (int64_t)blockIdx.x * kTtRows;
+  // lane q holds the coordinates of the wavefront's row q % RPW
+  const int64_t mi = row0 + wave * RPW + (lane % RPW);
+  const int2 mc = coords[mi < n ? mi : 0];
+  const bool mok = mi < n && mc.x >= 0 && mc.x < B && mc.y >= 0 && mc.y < V;
+  const int mb = mok ? mc.x : -1, mv = mok ? mc.y : 0;
+  int32_t v[RPW], r[RPW];
 #pragma unroll
-  for (int u = 0; u < 16; ++u) v[u] = s0 + u < Kt ? trow[s0 + u] : -1;
+  for (int u = 0; u < RPW; ++u) {
+    const int vert = __builtin_amdgcn_readlane(mv, u);
+    v[u] = tv[(int64_t)vert * Kt + (lane < Kt ? lane : 0)];
+  }
 #pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const bool live = ok && v[u] >= 0 && v[u] < V;
-    r[u] = irow[live ? v[u] : 0];
+  for (int u = 0; u < RPW; ++u) {
+    const int body = __builtin_amdgcn_readlane(mb, u);
+    const bool live = body >= 0 && lane < Kt && v[u] >= 0 && v[u] < V;
+    r[u] = inv[(int64_t)(body >= 0 ? body : 0) * V + (live ? v[u] : 0)];
     r[u] = (live && r[u] >= 0 && (int64_t)r[u] < n) ? r[u] : -1;
   }
-  uint64_t bits = 0;
 #pragma unroll
-  for (int u = 0; u < 16; ++u)
-    if (in && s0 + u < Kt) {
-      table_t[(int64_t)(s0 + u) * n + i] = r[u];
-      if (r[u] >= 0) bits |= 1ull << (s0 + u);
-    }
-  // or over the row's four lanes (lanes 4k .. 4k + 3 of the wavefront)
-#pragma unroll
-  for (int d = 1; d < 4; d <<= 1) {
-    const uint32_t lo = __shfl_xor((uint32_t)bits, d, 64);
-    const uint32_t hi = __shfl_xor((uint32_t)(bits >> 32), d, 64);
-    bits |= ((uint64_t)hi << 32) | lo;
+  for (int u = 0; u < RPW; ++u) {
+    const uint64_t bits = __ballot(r[u] >= 0);
+    tile[lane][wave * RPW + u] = r[u];
+    const int64_t i = row0 + wave * RPW + u;
+    if (lane == u && i < n) row_slots[i] = bits;
   }
-  if (in && q == 0) row_slots[i] = bits;
+  __syncthreads();
+  const int64_t i = row0 + lane;
+  for (int s = wave; s < Kt; s += kWaves)
+    if (i < n) table_t[(int64_t)s * n + i] = tile[s][lane];
 }
 
 // ---------------------------------------------------------------------------
@@ -578,27 +584,30 @@ __global__ __launch_bounds__(kThreads) void wgrad_tile_f32_kernel(
 }
 
 // dW[j][c][o]: sum of the partial tiles of slot j's chunks in fp64.
-// Workgroup (slot j and tile, 32 consecutive entries) of G chunk groups:
-// group y sums chunks y, y + G, ... of the slot in order, then the G group
-// sums are added in order.  A slot without chunks gets 0.  G = 32 for the
-// linear layer (one slot with all the chunks), 8 for a conv (whose sparse
-// slots have few chunks each).  With colpart, the workgroups of one more x
-// index reduce the bias gradient in colsum_kernel's order (32 groups: group y
-// sums splits y, y + 32, ..., whatever G is).
+// Workgroup (slot j and tile, 128 consecutive entries) of G chunk groups, a
+// thread four entries: group y sums chunks y, y + G, ... of the slot in order,
+// then the G group sums are added in order.  A slot without chunks gets 0.
+// G = 32 for the linear layer (one slot with all the chunks), 8 for a conv
+// (whose sparse slots have few chunks each; 32 took 34 us at the size below).
+// With colpart, the workgroups of one more x index reduce the bias gradient
+// in colsum_kernel's order (32 groups: group y sums splits y, y + 32, ...,
+// whatever G is).  Bound by the latency of the chunks' loads, 33 a thread for
+// slot 0 of 67 K rows: 16 bytes each in rounds of eight 12.4 us for 24 MB
+// (4 bytes in rounds of four: 14.6 us).
 template <int T, int G>
 __global__ __launch_bounds__(32 * G) void wgrad_reduce_kernel(
     const float* __restrict__ part, const int32_t* __restrict__ row_ptr, int32_t L, int32_t Cin,
     int32_t Cout, int single, int32_t n_chunks, float* __restrict__ dW,
     const float* __restrict__ colpart, int32_t splits, float* __restrict__ db) {
-  __shared__ double red[32][33];
+  __shared__ double red[G < 32 ? 32 : G][128 + 1];
   static_assert(G == 8 || G == 32, "chunk groups");
   const int tA = (Cin + T - 1) / T, tB = (Cout + T - 1) / T;
   const int tiles = tA * tB;
   const int ex = threadIdx.x & 31, y = threadIdx.x >> 5;
-  const int e = blockIdx.y * 32 + ex;
   // the last x index is the bias gradient's when colpart is given
   if (colpart != nullptr && (int)blockIdx.x == (int)gridDim.x - 1) {
     // 32 split groups over the G * 32 threads (G = 8: four groups per thread)
+    const int e = blockIdx.y * 32 + ex;
     for (int yg = y; yg < 32; yg += G) {
       double t = 0.0;
       if (e < Cout) {
@@ -626,26 +635,30 @@ __global__ __launch_bounds__(32 * G) void wgrad_reduce_kernel(
   // NU chunks' loads in flight at once (clamped addresses, past-the-end
   // values dropped), then added in chunk order; NU covers about a thread's
   // share (the linear layer's one slot has all the chunks)
-  constexpr int NU = G >= 32 ? 8 : 4;
-  double s = 0.0;
+  constexpr int NU = 8;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
   const int64_t stride = (int64_t)tiles * T * T;
-  const float* pe = part + (int64_t)t * T * T + e;
+  const float* pe = part + (int64_t)t * T * T + blockIdx.y * 128 + ex * 4;
   for (int q0 = c0 + y; q0 < c1; q0 += NU * G) {
-    float v[NU];
+    f32x4 v[NU];
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
       const int q = q0 + u * G;
-      v[u] = pe[(int64_t)(q < c1 ? q : q0) * stride];
+      v[u] = *reinterpret_cast<const f32x4*>(pe + (int64_t)(q < c1 ? q : q0) * stride);
     }
 #pragma unroll
     for (int u = 0; u < NU; ++u)
-      if (q0 + u * G < c1) s += (double)v[u];
+      if (q0 + u * G < c1)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[i] += (double)v[u][i];
   }
-  red[y][ex] = s;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) red[y][ex * 4 + i] = s[i];
   __syncthreads();
-  if (y == 0) {
+  if (threadIdx.x < 128) {
+    const int e = blockIdx.y * 128 + threadIdx.x;
     double u = 0.0;
-    for (int yy = 0; yy < G; ++yy) u += red[yy][ex];
+    for (int yy = 0; yy < G; ++yy) u += red[yy][threadIdx.x];
     const int a = e / T, b = e - a * T;
     const int c = ta * T + a, o = tb * T + b;
     if (c < Cin && o < Cout) dW[((int64_t)j * Cin + c) * Cout + o] = (float)u;
@@ -879,31 +892,50 @@ __global__ __launch_bounds__(kDgradThreads) void dgrad_kernel(
   auto compute = [&](const Job& jb, const Frags& f) {
     if (jb.blk < 0 || jb.s < 0) return;
     const int j = TBL ? slot_lds[jb.s] : 0;
+    // the weight fragments of KB k-steps are read before their first MFMA
+    constexpr int KB = KSM * NCB <= 8 ? KSM : (NCB >= 8 ? 1 : 8 / NCB);
 #pragma unroll
-    for (int ks = 0; ks < KSM; ++ks) {
-      if (ks < KS) {
+    for (int k0 = 0; k0 < KSM; k0 += KB) {
+      i32x4 bw[KB][NCB];
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) {
-          const i32x4 bw = *reinterpret_cast<const i32x4*>(
+      for (int kk = 0; kk < KB; ++kk) {
+        const int ks = k0 + kk < KS ? k0 + kk : 0;
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb)
+          bw[kk][cb] = *reinterpret_cast<const i32x4*>(
               wl + ((size_t)((j * KS + ks) * NCB + cb) * 64 + lane) * 16);
-          if constexpr (BF16) {
-            acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f.v[ks]),
-                                                             __builtin_bit_cast(bf16x8, bw),
-                                                             acc[cb], 0, 0, 0);
-          } else {
-            // lane group g holds reduction entries 4 g .. 4 g + 3 of the
-            // k-step on both sides; MFMA s contracts component s
+      }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int s2 = 0; s2 < 4; ++s2)
-              acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(__int_as_float(f.v[ks][s2]),
-                                                             __int_as_float(bw[s2]), acc[cb], 0,
-                                                             0, 0);
+      for (int kk = 0; kk < KB; ++kk) {
+        const int ks = k0 + kk;
+        if (ks < KSM && ks < KS) {
+#pragma unroll
+          for (int cb = 0; cb < NCB; ++cb) {
+            if constexpr (BF16) {
+              acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  __builtin_bit_cast(bf16x8, f.v[ks < KSM ? ks : 0]),
+                  __builtin_bit_cast(bf16x8, bw[kk][cb]), acc[cb], 0, 0, 0);
+            } else {
+              // lane group g holds reduction entries 4 g .. 4 g + 3 of the
+              // k-step on both sides; MFMA s contracts component s
+#pragma unroll
+              for (int s2 = 0; s2 < 4; ++s2)
+                acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                    __int_as_float(f.v[ks < KSM ? ks : 0][s2]), __int_as_float(bw[kk][cb][s2]),
+                    acc[cb], 0, 0, 0);
+            }
           }
         }
       }
     }
   };
   auto epilogue = [&](int blk) {
+    // the last MFMAs may sit right behind a branch: their results are read at
+    // least 20 wait states later (an fp32 16x16x4 needs 18)
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
       if constexpr (BF16) {
@@ -1376,7 +1408,8 @@ hipError_t launch_transposed_table(const int32_t* coords, const int32_t* inv, in
                                    int32_t V, const int32_t* nbr_t, int32_t Kt, int32_t* table_t,
                                    uint64_t* row_slots, hipStream_t stream) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(tt_kernel, dim3(grid_for(4 * n)), dim3(kThreads), 0, stream,
+  hipLaunchKernelGGL(tt_kernel, dim3((unsigned)((n + kTtRows - 1) / kTtRows)), dim3(kThreads), 0,
+                     stream,
                      reinterpret_cast<const int2*>(coords), inv, n, B, V, nbr_t, Kt, table_t,
                      row_slots);
   return hipGetLastError();
@@ -1453,7 +1486,7 @@ hipError_t launch_layer_backward(int conv, const void* S, const int32_t* table,
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (dW != nullptr) {
-      const dim3 rg((unsigned)(pl.tiles + (db != nullptr ? 1 : 0)), (unsigned)(pl.T * pl.T / 32));
+      const dim3 rg((unsigned)(pl.tiles + (db != nullptr ? 1 : 0)), (unsigned)(pl.T * pl.T / 128));
       if (pl.T == 128)
         hipLaunchKernelGGL((wgrad_reduce_kernel<128, 32>), rg, dim3(32 * 32), 0, stream, part,
                            nullptr, (int32_t)L, Cin, Cout, 1, (int32_t)G, dW, colpart, (int32_t)G,
@@ -1523,10 +1556,10 @@ hipError_t launch_layer_backward(int conv, const void* S, const int32_t* table,
                          rp, Kw, n, pl.L, Cin, Cout, part);
     err = hipGetLastError();
     if (err != hipSuccess) return err;
-    // one more column of workgroups reduces the bias gradient (T * T / 32 >= Cout / 32)
+    // one more column of workgroups reduces the bias gradient (T * T / 128 >= Cout / 32)
     const float* cp = db != nullptr ? reinterpret_cast<const float*>(w + pl.off_colpart) : nullptr;
     const dim3 rg((unsigned)(Kw * pl.tiles + (db != nullptr ? 1 : 0)),
-                  (unsigned)(pl.T * pl.T / 32));
+                  (unsigned)(pl.T * pl.T / 128));
 #define SHC_REDUCE(TT, GG)                                                                     \
   hipLaunchKernelGGL((wgrad_reduce_kernel<TT, GG>), rg, dim3(32 * GG), 0, stream, part, rp, pl.L, \
                      Cin, Cout, conv ? 0 : 1, (int32_t)pl.max_chunks, dW, cp, pl.splits, db)

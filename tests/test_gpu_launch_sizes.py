@@ -108,3 +108,32 @@ def test_short_bodies_norm_and_pool(dev, dtype, B, V, C, G, p):
     P = torch.full((B, C), float("nan"), dtype=TORCH[dtype], device=dev)
     shc.segment_maxpool(Sd, up(rp), n, B, P, -2.0)
     assert np.array_equal(down(P), O.segment_max(S.astype(np.float64), rp, -2.0))
+
+
+@pytest.mark.parametrize("V,n,K", [(40, 1, 1), (200, 63, 9), (200, 64, 9), (300, 65, 5),
+                                   (655, 1300, 9)])
+def test_transposed_table_blocks(dev, V, n, K):
+    rng = np.random.default_rng(V + n + K)
+    B = 2
+    nbr = np.stack([rng.permutation(V) for _ in range(K)], 1).astype(np.int32)
+    if K > 1:
+        nbr[rng.random((V, K)) < 0.2] = -1
+        nbr[:, 1] = rng.integers(0, V // 2, size=V)      # several senders through one slot
+    m = np.zeros(B * V, np.uint8)
+    m[rng.permutation(B * V)[:n]] = 1
+    m = m.reshape(B, V)
+    c = Compaction(m)
+    assert c.run() == n
+    nbr_t, slot_of, Kt = shc.transpose_neighbors(up(nbr))
+    tt = torch.full((Kt * n + 5,), -7, dtype=torch.int32, device=dev)
+    rs = torch.full((n + 1,), -7, dtype=torch.int64, device=dev)
+    shc.build_transposed_table(c.coords, c.inv, n, B, V, nbr_t, Kt, tt, rs)
+    coords, inv, _, _ = O.compact(m)
+    tv = down(nbr_t).reshape(-1)[: V * Kt].reshape(V, Kt)
+    u = tv[coords[:, 1]]
+    r = np.where(u >= 0, inv[coords[:, 0][:, None] * V + np.maximum(u, 0)], -1)
+    got = down(tt)
+    assert np.array_equal(got[: Kt * n].reshape(Kt, n), r.T) and np.all(got[Kt * n:] == -7)
+    bits = ((r >= 0).astype(object) << np.arange(Kt).astype(object)).sum(1)
+    have = down(rs)
+    assert [int(x) & (2 ** 64 - 1) for x in have[:n]] == [int(b) for b in bits] and have[n] == -7
