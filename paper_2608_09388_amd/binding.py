@@ -71,6 +71,7 @@ class StackDesc(ctypes.Structure):
 
 
 STACK_FEED_FN = ctypes.CFUNCTYPE(ctypes.c_int, _c_ptr, _c_i64, _c_ptr)
+_NO_FEED = STACK_FEED_FN()  # the NULL callback
 _SIGS = {
     "shc_status_string": (ctypes.c_char_p, [ctypes.c_int]),
     "shc_last_error": (ctypes.c_char_p, []),
@@ -648,7 +649,7 @@ class StackExecutor:
                 err.append(e)
                 return 1
 
-        cb = STACK_FEED_FN(_feed) if feed is not None else ctypes.cast(None, STACK_FEED_FN)
+        cb = STACK_FEED_FN(_feed) if feed is not None else _NO_FEED
         ev = None
         if time_events is not None:
             if len(time_events) != 2 * steps:

@@ -545,7 +545,18 @@ class SparseStack:
             self._bracket[1].wait(cur)
 
     def step(self) -> int:
-        """One pass of the whole path over the workload's batch, on its own."""
+        """One pass of the whole path over the workload's batch, on its own
+        (on a serial stack from the library's loop: after the count arrives the
+        GPU waits for each launch, which costs the host less from there)."""
+        if self._native is not None and self.side is None:
+            cur = self._enter()
+            try:
+                n, self._cur, self.prev_n = self._native.run(
+                    1, self.main, cur_set=self._cur, prev_rows=self.prev_n)
+            finally:
+                self._leave(cur)
+            self._set.n = n
+            return n
         cur = self._enter()
         s = self._set
         s.n = s.compact()

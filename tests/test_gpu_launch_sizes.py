@@ -12,6 +12,7 @@ import torch
 from oracle import shc_oracle as O
 from paper_2608_09388_amd import binding as shc
 from paper_2608_09388_amd import synth
+from paper_2608_09388_amd.pipeline import SparseStack
 from tests.gpu_util import (TORCH, Compaction, assert_gn_close, down, gn_floor, require_gpu, up)
 
 pytestmark = pytest.mark.gpu
@@ -137,3 +138,45 @@ def test_transposed_table_blocks(dev, V, n, K):
     bits = ((r >= 0).astype(object) << np.arange(Kt).astype(object)).sum(1)
     have = down(rs)
     assert [int(x) & (2 ** 64 - 1) for x in have[:n]] == [int(b) for b in bits] and have[n] == -7
+
+
+@pytest.mark.parametrize("incremental", [False, True])
+def test_stack_schedules(dev, incremental):
+    """The native loop's three-stream schedule (9 batches of 314 K entries, no
+    feed) against a serial stack's and the Python loop's, bit for bit, after a
+    run short enough for one stream and before one with a feed; step() on a
+    serial stack."""
+    B, V, K, C = 30, 10475, 9, 32
+    rng = np.random.default_rng(5)
+    _, nbr = synth.mesh("ellipsoid", V, K, 4)
+    masks = [(rng.random((B, V)) < p).astype(np.uint8) for p in (0.05, 0.04)]
+    x = synth.as_dtype(rng.standard_normal((B * V, C)).astype(np.float32), "bf16")[1]
+
+    def values(*shape):
+        w = rng.standard_normal(shape) / np.sqrt(np.prod(shape[:-1]))
+        return synth.as_dtype(w.astype(np.float32).reshape(-1), "bf16")[1].reshape(shape)
+
+    w = synth.Workload("schedules", B, V, K, "bf16", np.zeros((0, 3)), nbr, masks[0], x,
+                       [synth.Layer("linear", C, C, values(C, C), None, True),
+                        synth.Layer("conv", C, C, values(K, C, C), None, True)],
+                       pool=True, scatter=True)
+    dm = [up(m.reshape(-1)) for m in masks]
+
+    def drive(st):
+        out = []
+        for steps, feed in ((2, None), (9, None), (3, lambda k: st.mask.copy_(dm[k % 2])),
+                            (8, None), (1, None)):
+            n = st.run(steps, feed=feed)
+            torch.cuda.synchronize()
+            out += [n, st.dense_out.clone(), st.pooled.clone(), st.acts[-1][:n].clone()]
+        if st.side is None:
+            n = st.step()
+            torch.cuda.synchronize()
+            assert n == out[-4] and torch.equal(st.dense_out, out[-3])
+        return out
+
+    runs = [drive(SparseStack(w, side_stream=side, executor=ex, incremental_scatter=incremental))
+            for side, ex in ((True, "native"), (False, "native"), (True, "python"))]
+    for other in runs[1:]:
+        for a, b in zip(runs[0], other):
+            assert a == b if isinstance(a, int) else torch.equal(a, b)
