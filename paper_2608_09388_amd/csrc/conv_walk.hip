@@ -25,19 +25,32 @@
 // rows), so a lane ends with whole 16-byte runs of columns of one row and
 // stores them without an LDS pass.  Each output element is summed over the
 // slots in order and within a slot over the k-steps in order, as in the other
-// conv kernels: where they run the same shape the results are the same bits.
+// conv kernels: where they run the same shape the results are the same bits
+// (but for the split below).
+//
+// fp32 in the largest workgroups takes each product as six bf16 ones (SPLIT):
+// an fp32 value is three bf16 terms h + m + l exactly (8 + 8 + 8 significand
+// bits), the products h h, h m, m h, m m, h l and l h are exact in fp32 and are
+// summed there, and what is left out (m l, l m, l l) is below 2^-24 of a
+// product.  Six 16-bit MFMAs of 32 entries take 96 cycles, eight fp32 ones 256.
+// The sums have fewer roundings than the fp32 chain (six a 32-entry k-step
+// instead of eight): 2-norm error against 64 bits 3.7e-7 instead of 4.3e-7 at
+// K Cin = 576 (cap mask), 3.3e-7 instead of 3.8e-7 at 1,152, 1.3e-7 instead of
+// 1.5e-7 at 288.  The rows' terms are formed in registers, the weights' as they
+// are stored to LDS (three planes).
 //
 // What bounds it.  Few rows: the chain of phases, each about 0.6 us (barrier,
 // LDS write to read, a dependent MFMA chain), so 16-row workgroups spread over
 // the CUs (262 rows, K = 9, fp32 16 -> 64: 16.8 us before, in five workgroups
 // of the weight-stationary kernel, 6.9 us here; 1,965 rows 128 -> 128 fp32:
 // 96 -> 18.6 us; 1,965 rows bf16 256 -> 256: 56 -> 15.8 us).  Many rows in
-// fp32: the fp32 matrix rate (a 128-row phase takes 1.75 us of a CU, 153
-// TFLOP/s chip-wide) plus the index prologue of every workgroup (499 K rows
-// 64 -> 64 with 0.91 of the slots present: 400 -> 370 us; 32 K rows
-// 128 -> 128: 117 -> 80 us).  Many rows in bf16: the weight stage per 128 rows
-// (93 K rows, K = 5, 32 -> 80: 30 -> 26 us; 19 K rows, K = 7, 48 -> 80 from
-// coordinates: 16.2 -> 11.7 us).
+// fp32: the fp32 matrix rate held it at 370 us for 499 K rows 64 -> 64 with
+// 0.91 of the slots present (400 us in the tiled kernel); split, 279 us, bound
+// by the VALU work of the split, the LDS reads of three planes and the MFMAs
+// at about equal shares, and the index prologue of every workgroup (32 K rows
+// 128 -> 128: 117, 84 and 53 us; 26 K rows 256 -> 256: 259, 222 and 160 us).
+// Many rows in bf16: the weight stage per 128 rows (93 K rows, K = 5, 32 -> 80:
+// 30 -> 26 us; 19 K rows, K = 7, 48 -> 80 from coordinates: 16.2 -> 11.7 us).
 #include <mutex>
 
 #include "shc_internal.h"
@@ -69,19 +82,52 @@ typedef uint32_t walk_v2u32 __attribute__((ext_vector_type(2)));
 
 // weight row in LDS: fp32 rows padded by 16 bytes (the four rows a lane group
 // apart then start 16 banks apart); bf16 rows unpadded, 32-byte chunks swizzled
-__host__ __device__ constexpr int walk_wrow(bool bf16, int bn) { return bf16 ? bn * 2 : bn * 4 + 16; }
-__host__ __device__ constexpr int walk_wbuf(bool bf16, int bn) {
-  return kPhaseSteps * (bf16 ? 32 : 16) * walk_wrow(bf16, bn);
+// (split fp32: three bf16 planes)
+__host__ __device__ constexpr int walk_wrow(bool bf16, bool split, int bn) {
+  return bf16 || split ? bn * 2 : bn * 4 + 16;
+}
+__host__ __device__ constexpr int walk_wbuf(bool bf16, bool split, int bn) {
+  return (split ? 3 : 1) * kPhaseSteps * (bf16 ? 32 : 16) * walk_wrow(bf16, split, bn);
 }
 // index area (words): srcs [K][R]; sorted: srcs_in [K][R], perm [R], cnt [K],
-// hist [K + 2]; blkmask [R / 16]
+// hist [K + 2], w_wild; blkmask [R / 16]
 __host__ __device__ constexpr int walk_idx_bytes(int K, int R, bool sorted) {
-  return 4 * (K * R + R / 16 + (sorted ? K * R + R + 2 * K + 2 : 0));
+  return 4 * (K * R + R / 16 + (sorted ? K * R + R + 2 * K + 3 : 0));
 }
+
+// A pair of fp32 values as three bf16 pairs, x = h + m + l exactly: each term
+// is the nearest bf16 to what is left, 8 + 8 + 8 significand bits.  *big takes
+// the larger magnitude (a NaN is ignored: it stays one in h and in every
+// product, as in fp32).
+__device__ __forceinline__ void split3(walk_v2u32 x, uint32_t* h, uint32_t* m, uint32_t* l,
+                                       float* big) {
+  const float x0 = __uint_as_float(x[0]), x1 = __uint_as_float(x[1]);
+  *big = fmaxf(fmaxf(*big, fabsf(x0)), fabsf(x1));
+  const uint32_t hh = __builtin_bit_cast(
+      uint32_t, __builtin_convertvector(walk_f32x2{x0, x1}, walk_bf16x2));
+  const float r0 = x0 - __uint_as_float(hh << 16), r1 = x1 - __uint_as_float(hh & 0xFFFF0000u);
+  const uint32_t mm = __builtin_bit_cast(
+      uint32_t, __builtin_convertvector(walk_f32x2{r0, r1}, walk_bf16x2));
+  const float s0 = r0 - __uint_as_float(mm << 16), s1 = r1 - __uint_as_float(mm & 0xFFFF0000u);
+  *h = hh;
+  *m = mm;
+  *l = __builtin_bit_cast(uint32_t,
+                          __builtin_convertvector(walk_f32x2{s0, s1}, walk_bf16x2));
+}
+
+// The split product is used while a lane's 16 input values of a phase and a
+// thread's weights of one have their largest magnitude in these ranges (or are
+// all zero): below 2^-100 the third terms would leave bf16's range, and the
+// upper limits keep every product and partial sum of the terms finite where
+// the fp32 product is.  A wavefront that meets others computes its rows again
+// on the fp32 matrix cores.
+constexpr float kSplitMin = 0x1p-100f;
+constexpr float kSplitMaxA = 0x1p96f;
+constexpr float kSplitMaxW = 0x1p24f;
 
 // NA: register sets of input rows (NA - 1 phases in flight); NWS: register
 // sets of weights; MINW: wavefronts per SIMD that the registers must allow.
-template <bool BF16, int RW, int CW, int NCT, int NA, int NWS, int MINW>
+template <bool BF16, int RW, int CW, int NCT, int NA, int NWS, int MINW, bool SPLIT>
 __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs a) {
   constexpr int NT = 64 * RW * CW;
   constexpr int E = BF16 ? 2 : 4;
@@ -90,8 +136,10 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
   constexpr int KC = kPhaseSteps * KSTEP;    // reduction entries per phase
   constexpr int R = RW * 16;
   constexpr int BN = CW * NCT * 16;
-  constexpr int WROW = walk_wrow(BF16, BN);
-  constexpr int WBUF = walk_wbuf(BF16, BN);
+  constexpr int WROW = walk_wrow(BF16, SPLIT, BN);
+  constexpr int WBUF = walk_wbuf(BF16, SPLIT, BN);
+  constexpr int WPL = KC * WROW;             // a plane of the split weights
+  static_assert(!SPLIT || (!BF16 && R >= 64), "the split is of fp32, in sorted workgroups");
   constexpr int VPR = BN * E / 16;
   constexpr int NWV = KC * VPR / NT;         // weight vectors per thread and phase
   static_assert(KC * VPR % NT == 0, "whole weight vectors per thread");
@@ -99,7 +147,7 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
   // fp32: P tiles interleave their columns (entry q of tile ct is column
   // P q + ct of the P tiles' 16 P), so one LDS read gives a lane its weights
   // of P tiles and it ends with 4 P consecutive columns of its row
-  constexpr int P = BF16 ? 1 : (NCT < 4 ? NCT : 4);
+  constexpr int P = BF16 || SPLIT ? 1 : (NCT < 4 ? NCT : 4);
   typedef float WVec __attribute__((ext_vector_type(P == 1 ? 2 : P)));  // (P = 1: scalar reads)
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -110,6 +158,8 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
   int32_t* perm = srcs_in + K * R;                                    // [R] position -> row
   int32_t* cnt = perm + R;                                            // [K]
   int32_t* hist = cnt + K;                                            // [K + 2]
+  // split: set once a weight outside the split's range has been staged
+  volatile int* w_wild = hist + K + 2;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -160,13 +210,31 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
   };
   auto store_w = [&](int buf, const i32x4 (&wv)[NWV]) {
     unsigned char* base = smem + buf * WBUF;
+    float big = 0.f;
 #pragma unroll
     for (int u = 0; u < NWV; ++u) {
       const int v = u * NT + tid;
       const int k = v / VPR;
       const int q = v % VPR;
-      const int col = BF16 ? (((q >> 1) ^ swz_row(k)) << 5) + ((q & 1) << 4) : q * 16;
-      *reinterpret_cast<i32x4*>(base + k * WROW + col) = wv[u];
+      if constexpr (SPLIT) {
+        // columns 4q .. 4q + 3 of row k, 8 bytes in each plane
+        const int col = (((q >> 2) ^ swz_row(k)) << 5) + ((q & 3) << 3);
+        const walk_v2u32 x = {(uint32_t)wv[u][0], (uint32_t)wv[u][1]};
+        const walk_v2u32 y = {(uint32_t)wv[u][2], (uint32_t)wv[u][3]};
+        uint32_t h0, m0, l0, h1, m1, l1;
+        split3(x, &h0, &m0, &l0, &big);
+        split3(y, &h1, &m1, &l1, &big);
+        unsigned char* p = base + k * WROW + col;
+        *reinterpret_cast<walk_v2u32*>(p) = walk_v2u32{h0, h1};
+        *reinterpret_cast<walk_v2u32*>(p + WPL) = walk_v2u32{m0, m1};
+        *reinterpret_cast<walk_v2u32*>(p + 2 * WPL) = walk_v2u32{l0, l1};
+      } else {
+        const int col = BF16 ? (((q >> 1) ^ swz_row(k)) << 5) + ((q & 1) << 4) : q * 16;
+        *reinterpret_cast<i32x4*>(base + k * WROW + col) = wv[u];
+      }
+    }
+    if constexpr (SPLIT) {
+      if (!(big == 0.f || (big >= kSplitMin && big < kSplitMaxW))) *w_wild = 1;
     }
   };
   i32x4 wreg[NWS][NWV];
@@ -175,6 +243,7 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
 
   // ---- index lists ------------------------------------------------------------
   if (tid < R / 16) blkmask[tid] = 0;
+  if (SPLIT && tid == 0) *w_wild = 0;
   if constexpr (SORT) {
     for (int q = tid; q < 2 * K + 2; q += NT) cnt[q] = 0;  // cnt and hist
   }
@@ -317,15 +386,18 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
   auto col_of = [&](int ct, int r) -> int { return cbase + (ct / P) * 16 * P + P * r + ct % P; };
   // accumulators start at the bias of their columns (row l16 of a block)
   f32x4 acc[NCT];
+  auto init_acc = [&]() {
 #pragma unroll
-  for (int ct = 0; ct < NCT; ++ct) {
-    f32x4 b = {0.f, 0.f, 0.f, 0.f};
-    if (a.bias != nullptr) {
+    for (int ct = 0; ct < NCT; ++ct) {
+      f32x4 b = {0.f, 0.f, 0.f, 0.f};
+      if (a.bias != nullptr) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) b[r] = col_of(ct, r) < Cout ? a.bias[col_of(ct, r)] : 0.f;
+        for (int r = 0; r < 4; ++r) b[r] = col_of(ct, r) < Cout ? a.bias[col_of(ct, r)] : 0.f;
+      }
+      acc[ct] = b;
     }
-    acc[ct] = b;
-  }
+  };
+  init_acc();
 
   i32x4 areg[NA][kPhaseSteps];
   uint32_t off[kPhaseSteps];  // of the phase whose loads go out next
@@ -370,6 +442,24 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
       }
     }
   };
+  // split weights: plane st % 3 of the 32-entry k-step st / 3, entries
+  // 4g .. 4g+3 of both its halves for column i
+  auto read_plane = [&](const unsigned char* base, int st, WFrag& f) {
+    const int r = 32 * (st / 3) + 4 * g + (l16 >> 2);
+    const int sw = swz_row(4 * g + (l16 >> 2));
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct) {
+      const unsigned char* p0 = base + (st % 3) * WPL + r * WROW +
+                                (((wc * NCT + ct) ^ sw) << 5) + 8 * (l16 & 3);
+      const walk_bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+          (SHC_WALK_LDS walk_bf16x4*)(const_cast<unsigned char*>(p0)));
+      const walk_bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+          (SHC_WALK_LDS walk_bf16x4*)(const_cast<unsigned char*>(p0 + 16 * WROW)));
+      const bf16x8 w = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      f.v[ct] = __builtin_bit_cast(i32x4, w);
+    }
+  };
+  bool wild = false;  // split: an input value outside its range was met
   auto phase = [&](int p, i32x4 (&cur)[kPhaseSteps], i32x4 (&ahead)[kPhaseSteps],
                    i32x4 (&wv)[NWV]) {
     // phase p's weights were stored before this barrier; every wavefront is
@@ -384,13 +474,59 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
     }
     const bool live = (all & bits) != 0u;
     WFrag wf[2];
-    if (live) read_w(base, 0, wf[0]);
+    if (live) {
+      if constexpr (SPLIT) read_plane(base, 0, wf[0]);
+      else read_w(base, 0, wf[0]);
+    }
     issue_a(off, ahead);
     store_w((p + 1) & 1, wv);
     load_w(p + 1 + NWS, wv);
     offsets(p + NA, off);
     if (!live) return;
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (SPLIT) {
+      float big = 0.f;  // the lane's largest input magnitude
+#pragma unroll
+      for (int ks = 0; ks < kPhaseSteps; ++ks)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) big = fmaxf(big, fabsf(__int_as_float(cur[ks][i])));
+      wild = wild || !(big == 0.f || (big >= kSplitMin && big < kSplitMaxA));
+      // two k-steps of 32 entries; lane group g holds entries 4g .. 4g+3 of
+      // each of their two 16-entry halves.  Stage (m, plane): the plane's
+      // weights by every input term that with it makes a product above 2^-24
+      // of the whole (h by l, m, h; m by m, h; l by h)
+      bf16x8 at[3];
+#pragma unroll
+      for (int st = 0; st < 6; ++st) {
+        const int m = st / 3, pl = st % 3;
+        if (pl == 0) {
+          walk_v4u32 t[3];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const i32x4& v = cur[2 * m + q / 2];
+            const walk_v2u32 x = {(uint32_t)v[2 * (q & 1)], (uint32_t)v[2 * (q & 1) + 1]};
+            uint32_t h, mm, l;
+            float unused = 0.f;
+            split3(x, &h, &mm, &l, &unused);
+            t[0][q] = h;
+            t[1][q] = mm;
+            t[2][q] = l;
+          }
+#pragma unroll
+          for (int q = 0; q < 3; ++q) at[q] = __builtin_bit_cast(bf16x8, t[q]);
+        }
+        if (st + 1 < 6) read_plane(base, st + 1, wf[(st + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 2 - pl; q >= 0; --q)
+#pragma unroll
+          for (int ct = 0; ct < NCT; ++ct)
+            acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(bf16x8, wf[st & 1].v[ct]), at[q], acc[ct], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      return;
+    }
 #pragma unroll
     for (int ks = 0; ks < kPhaseSteps; ++ks) {
       if (ks + 1 < kPhaseSteps) read_w(base, ks + 1, wf[(ks + 1) & 1]);
@@ -420,6 +556,39 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
 #pragma unroll
     for (int q = 0; q < U; ++q)
       phase(p0 + q, areg[q % NA], areg[(q + NA - 1) % NA], wreg[(q + 1) % NWS]);
+  }
+
+  if constexpr (SPLIT) {
+    if (__builtin_amdgcn_readfirstlane(*w_wild) != 0 || __ballot(wild) != 0) {
+      // this wavefront's rows again on the fp32 matrix cores, straight from memory
+      init_acc();
+#pragma unroll 1
+      for (int s = 0; s < nks; ++s) {
+        const int lo = slot_of(s * KSTEP), hi = slot_of(min((s + 1) * KSTEP, Ktot) - 1);
+        if ((all & ((2u << hi) - 1u) & ~((1u << lo) - 1u)) == 0u) continue;
+        const int kk = s * KSTEP + 4 * g;
+        const int j = kk < Ktot ? slot_of(kk) : 0;
+        const int32_t src = srcs[j * R + wr * 16 + l16];
+        const uint32_t aoff = (kk < Ktot && src >= 0)
+                                  ? ((uint32_t)src * (uint32_t)Cin + (uint32_t)(kk - j * Cin)) * E
+                                  : kWalkOutOfRange;
+        const i32x4 v = __builtin_bit_cast(
+            i32x4, __builtin_amdgcn_raw_buffer_load_b128(s_rsrc, aoff, 0, 0));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+#pragma unroll
+          for (int ct = 0; ct < NCT; ++ct) {
+            const int c = n0 + (wc * NCT + ct) * 16 + l16;
+            const uint32_t woff = (kk + i < Ktot && c < Cout)
+                                      ? ((uint32_t)(kk + i) * (uint32_t)Cout + (uint32_t)c) * E
+                                      : kWalkOutOfRange;
+            const int w = __builtin_amdgcn_raw_buffer_load_b32(w_rsrc, woff, 0, 0);
+            acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(__int_as_float(w),
+                                                           __int_as_float(v[i]), acc[ct], 0, 0, 0);
+          }
+        }
+      }
+    }
   }
 
   // ---- epilogue: activation, rounding, four columns of a row per store ---------
@@ -462,10 +631,10 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
   }
 }
 
-template <bool BF16, int RW, int CW, int NCT, int NA, int NWS, int MINW>
+template <bool BF16, int RW, int CW, int NCT, int NA, int NWS, int MINW, bool SPLIT = false>
 hipError_t launch_walk(const GemmArgs& a, hipStream_t stream) {
   constexpr int R = RW * 16, BN = CW * NCT * 16;
-  auto kern = conv_walk_kernel<BF16, RW, CW, NCT, NA, NWS, MINW>;
+  auto kern = conv_walk_kernel<BF16, RW, CW, NCT, NA, NWS, MINW, SPLIT>;
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [&] {
@@ -474,7 +643,7 @@ hipError_t launch_walk(const GemmArgs& a, hipStream_t stream) {
   });
   if (attr_err != hipSuccess) return attr_err;
   const size_t lds =
-      2 * walk_wbuf(BF16, BN) + walk_idx_bytes(a.K, R, R >= 64);
+      2 * walk_wbuf(BF16, SPLIT, BN) + walk_idx_bytes(a.K, R, R >= 64);
   const dim3 grid((unsigned)((a.n_rows + R - 1) / R), (unsigned)((a.Cout + BN - 1) / BN));
   hipLaunchKernelGGL(kern, grid, dim3(64 * RW * CW), lds, stream, a);
   return hipGetLastError();
@@ -485,11 +654,20 @@ hipError_t launch_walk(const GemmArgs& a, hipStream_t stream) {
 // rows 12.4 / 16.3 / 23.9 us, at 7,926 rows 17.4 / 17.0 / 24.2; 128 -> 128 at
 // 15,851 rows (992 workgroups of 128 x 32) 96 / 41.6 / 42.1, at 32,000 rows
 // 183 / 90 / 80; bf16 256 -> 256 at 7,926 rows 71 / 24.8 / 20.5.
+// The split's 128-row workgroups run two to a CU; 256 rows in 16 wavefronts
+// stage the weights half as often and win while one round of them covers the
+// rows (128 -> 128 at 32,000 rows 53 against 59 us; at 67,040 sparse rows 117
+// against 105).
 template <bool BF16>
-hipError_t launch_walk_rows(const GemmArgs& a, int num_cus, hipStream_t stream) {
+hipError_t launch_walk_rows(const GemmArgs& a, bool split, int num_cus, hipStream_t stream) {
   if (conv_walk_small(a, num_cus))
     return launch_walk<BF16, 1, 4, 1, 4, 4, 1>(a, stream);
   if (conv_walk_medium(a, num_cus, 2)) return launch_walk<BF16, 8, 1, 2, 2, 2, 4>(a, stream);
+  if constexpr (!BF16) {
+    if (split && ((a.n_rows + 255) / 256) * ((a.Cout + 63) / 64) <= num_cus)
+      return launch_walk<false, 16, 1, 4, 2, 1, 4, true>(a, stream);
+    if (split) return launch_walk<false, 8, 1, 4, 2, 1, 4, true>(a, stream);
+  }
   return launch_walk<BF16, 8, 1, 4, 2, 1, 4>(a, stream);
 }
 
@@ -504,11 +682,12 @@ bool conv_walk_supported(const GemmArgs& a, bool bf16) {
          (int64_t)a.K * a.Cin * a.Cout * e <= 0x7FFF0000LL;
 }
 
-hipError_t launch_conv_walk(const GemmArgs& a_in, bool bf16, int num_cus, hipStream_t stream) {
+hipError_t launch_conv_walk(const GemmArgs& a_in, bool bf16, bool split, int num_cus,
+                            hipStream_t stream) {
   GemmArgs a = a_in;
   a.cin_magic = (uint32_t)(((1ull << 32) + (uint64_t)a.Cin - 1) / (uint64_t)a.Cin);
-  return bf16 ? launch_walk_rows<true>(a, num_cus, stream)
-              : launch_walk_rows<false>(a, num_cus, stream);
+  return bf16 ? launch_walk_rows<true>(a, split, num_cus, stream)
+              : launch_walk_rows<false>(a, split, num_cus, stream);
 }
 
 }  // namespace shc

@@ -649,18 +649,26 @@ hipError_t launch_gather_gemm(const GemmArgs& a, bool conv, bool bf16, hipStream
   const bool walk = conv && conv_walk_supported(a, bf16);
   if (walk && bf16 && a.Cin == 64 && a.Cout == 128 && conv_sm_supported(a, bf16) &&
       conv_walk_medium(a, cus, 1))
-    return launch_conv_walk(a, bf16, cus, stream);
+    return launch_conv_walk(a, bf16, false, cus, stream);
   if (conv && conv_sm_supported(a, bf16) &&
       (a.n_rows >= 1000LL * cus || (a.Cin == 64 && a.n_rows <= 128LL * cus)))
     return launch_conv_sm(a, cus, stream);
   if (walk && !bf16 &&
       (conv_walk_small(a, cus) || (a.K * a.Cin <= 288 && conv_walk_medium(a, cus, 2))))
-    return launch_conv_walk(a, bf16, cus, stream);
+    return launch_conv_walk(a, bf16, false, cus, stream);
   WsPlan plan;
   if (ws_plan(a, conv, bf16, cus, &plan)) return launch_ws_gemm(a, conv, bf16, plan, stream);
   // a conv plan exists only for the weight-stationary kernel
   if (a.plan != nullptr || a.plan_out != nullptr) return hipErrorInvalidValue;
-  if (walk) return launch_conv_walk(a, bf16, cus, stream);
+  if (walk) {
+    // fp32 products split into bf16 ones only where no other kernel runs the
+    // shape from a table either (a conv from coordinates leaves the
+    // weight-stationary kernel by density), so that a conv gives the same bits
+    // from its table and from coordinates
+    GemmArgs t = a;
+    t.table = static_cast<const int32_t*>(a.S);  // (only its presence is read)
+    return launch_conv_walk(a, bf16, !ws_plan(t, conv, bf16, cus, &plan), cus, stream);
+  }
   // the linear layer, and convs whose buffers need 64-bit offsets
   if (bf16) return conv ? launch_typed<true, true>(a, stream) : launch_typed<true, false>(a, stream);
   return conv ? launch_typed<false, true>(a, stream) : launch_typed<false, false>(a, stream);

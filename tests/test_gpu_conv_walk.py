@@ -32,7 +32,10 @@ def dev():
     ("f32", 6, 700, 1000, 32, 32, 48),     # 32 slots
     ("f32", 40, 655, 9000, 9, 16, 64),     # 128 x 32 workgroups, a ragged last one
     ("f32", 30, 655, 8321, 3, 144, 144),   # 128 x 32, K Cin past a phase
-    ("f32", 40, 655, 20000, 9, 64, 128),   # 128 x 64, dense slots
+    ("f32", 40, 655, 17001, 9, 128, 128),  # split products, 256-row workgroups
+    ("f32", 40, 900, 23000, 20, 48, 80),   # the same, 20 slots of 48 channels
+    ("f32", 60, 655, 33500, 9, 128, 128),  # split products, 128-row workgroups
+    ("f32", 90, 655, 50001, 3, 144, 80),   # the same, K Cin past a phase
     ("bf16", 1, 40, 15, 9, 16, 16),        # a k-step over two slots
     ("bf16", 3, 500, 128, 7, 48, 80),      # k-steps that cross slots
     ("bf16", 5, 655, 1000, 9, 64, 128),    # the encoder's widening layer
@@ -74,3 +77,55 @@ def test_conv_walk_against_oracle(dev, dtype, B, V, n, K, Cin, Cout):
         scale = O.conv_at(S, coords, B, V, oob, W, rows, b, scale=True)
         assert_scaled_close(got[rows], ref, scale, dtype,
                             f"conv n={n} K={K} {Cin}->{Cout} act={act}", n_terms=K * Cin)
+
+
+@pytest.mark.parametrize("what", ["tiny rows", "huge rows", "infinite rows", "NaN rows",
+                                  "huge weights", "tiny weights"])
+def test_conv_walk_value_range(dev, what):
+    """fp32 products formed from bf16 terms, on values outside their range: the
+    rows and weights there go to the fp32 matrix cores, every other row stays
+    within the fp32 bound, and infinities and NaN come out as in 64 bits."""
+    B, V, n, K, Cin, Cout = 40, 655, 17001, 9, 128, 128
+    rng = np.random.default_rng(len(what))
+    nbr = rng.integers(0, V, size=(V, K)).astype(np.int32)
+    nbr[:, 0] = np.arange(V)
+    m = np.zeros(B * V, dtype=np.uint8)
+    m[rng.permutation(B * V)[:n]] = 1
+    m = m.reshape(B, V)
+    c = Compaction(m)
+    assert c.run() == n
+    S = rng.standard_normal((n, Cin)).astype(np.float32)
+    W = (rng.standard_normal((K, Cin, Cout)) / np.sqrt(K * Cin)).astype(np.float32)
+    odd = rng.choice(n, 40, replace=False)
+    if what == "tiny rows":
+        S *= np.float32(1e-33)
+    elif what == "huge rows":
+        S[odd] *= np.float32(1e36)
+    elif what == "infinite rows":
+        S[odd, 3] = np.inf
+        S[odd[:10], 5] = -np.inf
+    elif what == "NaN rows":
+        S[odd, 7] = np.nan
+    elif what == "huge weights":
+        W[2] *= np.float32(1e30)
+    else:
+        W *= np.float32(1e-34)
+    coords, _, _, _ = O.compact(m)
+    rows = np.unique(np.concatenate([odd, np.arange(300), rng.choice(n, 500, replace=False)]))
+    nd = up(nbr)
+    table = torch.empty(K * n, dtype=torch.int32, device=dev)
+    shc.build_neighbor_table(c.coords, c.inv, n, B, V, nd, table)
+    out = torch.full((n, Cout), float("nan"), dtype=torch.float32, device=dev)
+    shc.sparse_neighbor_conv_table(up(S), table, n, up(W), None, out, shc.SHC_ACT_NONE)
+    got = down(out)[rows]
+    with np.errstate(all="ignore"):
+        ref = O.conv_at(S.astype(np.float64), coords, B, V, nbr, W.astype(np.float64), rows, None)
+        scale = O.conv_at(S.astype(np.float64), coords, B, V, nbr, W.astype(np.float64), rows,
+                          None, scale=True)
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    inf = np.isinf(ref)
+    assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], ref[inf])
+    ok = np.isfinite(ref)
+    # 1e-5 of the abs-sum scale, and the spacing of fp32's smallest numbers for
+    # each of the K Cin products and sums below its normal range
+    assert np.all(np.abs(got[ok] - ref[ok]) <= 1e-5 * scale[ok] + 2 * K * Cin * 2.0 ** -149)
