@@ -359,7 +359,7 @@ __device__ inline int pair_index(int i, int k, int K) {  // i <= k
   return i * K - i * (i - 1) / 2 + (k - i);
 }
 
-// One workgroup of kScoreThreads threads.  F of each pair: a wavefront per
+// One workgroup of up to kScoreThreads threads.  F of each pair: a wavefront per
 // pair sums its parts (lane j: parts j, j + 64, ...; then a fixed butterfly
 // over the lanes), four pairs' loads and butterflies at a time: the launch is
 // one workgroup's chain of memory round trips (ten masks, 55 pairs of 64
@@ -373,13 +373,14 @@ __global__ __launch_bounds__(kScoreThreads) void score_kernel(
   __shared__ double a[kMaxScoreMasks];
   const int P = K * (K + 1) / 2;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  constexpr int kPairs = 4, kScoreWaves = kScoreThreads / 64;
-  for (int p0 = wave; p0 < P; p0 += kPairs * kScoreWaves) {
+  constexpr int kPairs = 4;
+  const int waves = blockDim.x / 64;
+  for (int p0 = wave; p0 < P; p0 += kPairs * waves) {
     double s[kPairs] = {0.0, 0.0, 0.0, 0.0};
     for (int t = lane; t < parts; t += 64) {
 #pragma unroll
       for (int u = 0; u < kPairs; ++u) {
-        const int p = p0 + u * kScoreWaves;
+        const int p = p0 + u * waves;
         s[u] += fq[(int64_t)(p < P ? p : p0) * parts + t];
       }
     }
@@ -389,7 +390,7 @@ __global__ __launch_bounds__(kScoreThreads) void score_kernel(
       for (int u = 0; u < kPairs; ++u) s[u] += __shfl_xor(s[u], m);
 #pragma unroll
     for (int u = 0; u < kPairs; ++u)
-      if (lane == 0 && p0 + u * kScoreWaves < P) F[p0 + u * kScoreWaves] = s[u];
+      if (lane == 0 && p0 + u * waves < P) F[p0 + u * waves] = s[u];
   }
   __syncthreads();
   const int k = threadIdx.x;
@@ -481,6 +482,9 @@ BlockPlan block_plan(int32_t K, int64_t N, int32_t C) {
   return b;
 }
 
+// threads of the score launch: four wavefronts hold 16 pairs at once
+int score_threads(int32_t K) { return K * (K + 1) / 2 <= 16 ? 256 : kScoreThreads; }
+
 }  // namespace
 
 size_t mask_scores_workspace_bytes(int32_t K, int64_t N, int32_t C) {
@@ -519,7 +523,7 @@ hipError_t launch_mask_scores(const void* O, int32_t K, int64_t N, int32_t C,
                        dim3(256), 0, stream, part, b.splits, K, C, b.nb, b.chunks, fq);
     err = hipGetLastError();
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(score_kernel, dim3(1), dim3(kScoreThreads), 0, stream, fq, b.chunks, K,
+    hipLaunchKernelGGL(score_kernel, dim3(1), dim3(score_threads(K)), 0, stream, fq, b.chunks, K,
                        alpha_in, alpha_out, sim, kappa, top);
     return hipGetLastError();
   }
@@ -542,7 +546,7 @@ hipError_t launch_mask_scores(const void* O, int32_t K, int64_t N, int32_t C,
                      0, stream, part, splits, T * T, chunks, ft);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(score_kernel, dim3(1), dim3(kScoreThreads), 0, stream, ft, tiles * chunks, K,
+  hipLaunchKernelGGL(score_kernel, dim3(1), dim3(score_threads(K)), 0, stream, ft, tiles * chunks, K,
                      alpha_in, alpha_out, sim, kappa, top);
   return hipGetLastError();
 }
