@@ -173,20 +173,27 @@ __global__ __launch_bounds__(kGramThreads) void gram_tile_kernel(const __bf16* _
 // K C columns, mask-major), for C in {64, 128, 256}, i.e. 256 / C masks per
 // 256-column block.  Workgroup (block pair ba <= bb, row split) accumulates
 // M[:, 256 ba ..]^T M[:, 256 bb ..] over its rows: twice the flops per loaded
-// byte of the T x T pair tiles above.  Four wavefronts, each a 128 x 128
-// quarter (64 accumulator blocks); rows go through one padded LDS stage R at
-// a time, the next step loaded into registers meanwhile.  Workgroups are
-// dealt to the XCDs split-major, as for the pair tiles.
+// byte of the T x T pair tiles above.  Eight wavefronts, each a 128 x 64 part
+// (32 accumulator blocks); rows go through two LDS stages R at a time, one
+// barrier per step: a step's rows are stored at the start of the step before,
+// from registers loaded during the one before that.  The 32-byte column chunk
+// c of staged row r sits at c ^ (r & 3 | (r >> 3 & 1) << 2); with rows padded
+// by 16 bytes neighbouring rows shared banks, so that the 12 fragments a
+// wavefront reads for 32 MFMAs conflicted two ways.  Workgroups are dealt to
+// the XCDs split-major, as for the pair tiles.  Ten masks of 167,600 rows x
+// 128: the whole score call takes 318 us with one padded stage and two
+// barriers a step, 310 us so.  One workgroup fills a CU's LDS, and its
+// fragment reads are by count three quarters as long as its MFMAs.
 template <int R>
 __global__ __launch_bounds__(kBlockThreads) void gram_block_kernel(const __bf16* __restrict__ O, int32_t K, int64_t N, int32_t C,
                        int64_t rows_per_split, int32_t splits, int32_t nb,
                        float* __restrict__ part) {
   constexpr int T = 256;
   constexpr int NA = 8, NBB = 4;              // 16-column blocks per wavefront: A side, B side
-  constexpr int ROW = T * 2 + 16;             // padded LDS row (bytes)
+  constexpr int ROW = T * 2;                  // LDS row (bytes)
   constexpr int VPR = T * 2 / 16;             // 16-byte vectors per staged row
   constexpr int LOADS = 2 * R * VPR / kBlockThreads;
-  __shared__ __attribute__((aligned(16))) unsigned char stage[2][R * ROW];
+  __shared__ __attribute__((aligned(16))) unsigned char stage[2][2][R * ROW];  // [step & 1][side]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 4, l16 = lane & 15;
@@ -230,17 +237,22 @@ __global__ __launch_bounds__(kBlockThreads) void gram_block_kernel(const __bf16*
           (okB && okr) ? *reinterpret_cast<const i32x4*>(baseB + r * C) : i32x4{0, 0, 0, 0};
     }
   };
-  auto store = [&](const i32x4* v) {
+  auto swz = [](int r) -> int { return (r & 3) | (((r >> 3) & 1) << 2); };
+  auto store = [&](int buf, const i32x4* v) {
 #pragma unroll
     for (int u = 0; u < LPO; ++u) {
       const int rr = rbase + u * RSTEP;
-      *reinterpret_cast<i32x4*>(&stage[0][rr * ROW + q * 16]) = v[u];
-      *reinterpret_cast<i32x4*>(&stage[1][rr * ROW + q * 16]) = v[LPO + u];
+      const int at = rr * ROW + (((q >> 1) ^ swz(rr)) << 5) + ((q & 1) << 4);
+      *reinterpret_cast<i32x4*>(&stage[buf][0][at]) = v[u];
+      *reinterpret_cast<i32x4*>(&stage[buf][1][at]) = v[LPO + u];
     }
   };
-  // rows 8g .. 8g+7 of channel 16 cb + l16 of one staged operand
+  // rows 8g .. 8g+7 of channel 16 cb + l16 of one staged operand (the swizzle
+  // of rows 8g + (l16 >> 2) and 4 more is one, a per-lane constant)
+  const int sw = swz(8 * g + (l16 >> 2));
   auto frag = [&](const unsigned char* base, int cb) -> bf16x8 {
-    const unsigned char* p0 = base + (8 * g + (l16 >> 2)) * ROW + cb * 32 + 8 * (l16 & 3);
+    const unsigned char* p0 =
+        base + (8 * g + (l16 >> 2)) * ROW + ((cb ^ sw) << 5) + 8 * (l16 & 3);
     const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
         (SHC_LDS bf16x4*)(const_cast<unsigned char*>(p0)));
     const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
@@ -255,25 +267,30 @@ __global__ __launch_bounds__(kBlockThreads) void gram_block_kernel(const __bf16*
     for (int y = 0; y < NBB; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   i32x4 v[LOADS];
-  if (steps > 0) load(0, v);
+  if (steps > 0) {
+    load(0, v);
+    store(0, v);
+    load(1, v);  // (past the last row: zeros)
+  }
   for (int st = 0; st < steps; ++st) {
-    store(v);
-    __syncthreads();
-    if (st + 1 < steps) load(st + 1, v);
+    __syncthreads();  // step st is stored; every wavefront is done with step st - 1
+    store((st + 1) & 1, v);
+    load(st + 2, v);
+    const unsigned char* sa = stage[st & 1][0];
+    const unsigned char* sb = stage[st & 1][1];
 #pragma unroll
     for (int sub = 0; sub < R / 32; ++sub) {
       bf16x8 fb[NBB];
 #pragma unroll
-      for (int y = 0; y < NBB; ++y) fb[y] = frag(stage[1] + sub * 32 * ROW, wb * NBB + y);
+      for (int y = 0; y < NBB; ++y) fb[y] = frag(sb + sub * 32 * ROW, wb * NBB + y);
 #pragma unroll
       for (int x = 0; x < NA; ++x) {
-        const bf16x8 fa = frag(stage[0] + sub * 32 * ROW, wa * NA + x);
+        const bf16x8 fa = frag(sa + sub * 32 * ROW, wa * NA + x);
 #pragma unroll
         for (int y = 0; y < NBB; ++y)
           acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fb[y], acc[x][y], 0, 0, 0);
       }
     }
-    __syncthreads();
   }
   // partial block, row-major [T][T]: lane (g, l16) holds rows 4g .. 4g+3 of column l16
   float* out = part + ((int64_t)item * splits + split) * T * T;
