@@ -3,16 +3,30 @@
 //
 //   out[i] = act( bias + sum_{j<K} S[table[j][i]] W[j] ),  absent entries add 0.
 //
-// A workgroup owns 128 or 256 consecutive active rows and every output
+// A workgroup owns 128 or 320 consecutive active rows and every output
 // column.  It walks the slots in order: the weights of slot j (Cin x Cout)
 // sit in LDS while every wavefront multiplies its rows' slot-j neighbour rows
 // by them, and slot j + 1's weights are loaded beside that work into the
-// other of two buffers; the neighbour rows of slot j + 2 (and j + 1) are in
-// flight in registers meanwhile.  Each gathered row therefore feeds all Cout
+// other of two buffers; the neighbour rows of slot j + 1 are in flight in
+// registers meanwhile.  Each gathered row therefore feeds all Cout
 // columns at once, and the index work per row group is one pass over its
 // table entries (no sort, no job lists).  A (16-row block, slot) pair with
 // no present row is skipped.  Accumulation is in fp32, per output element
 // in slot order and within a slot in k order.
+//
+// What bounds it: a slot's weight reads from LDS and its MFMAs take about as
+// long each, and the table reads, the sort and the output around the slots
+// would stand beside neither.  So a workgroup takes half a CU's LDS or less
+// (128 rows, the output staged where the weights were) and two or more share
+// a CU, one's slots under another's ends; with one of 256 rows a CU those ends
+// were 59 of 273 us (670,464 rows at half density, 128 -> 128 channels, nine
+// slots; 257 us with two).  At 600,000 rows, half dense: 64 -> 128 149 ->
+// 130 us, 128 -> 64 170 -> 136; seven slots 128 -> 128 278 -> 215.  Sparse
+// masks at 128 -> 128 and nine slots are even (10%, 600,000 rows: 213, 212) or
+// pay a little for weights loaded per 128 rows (5%, 258,000: 81, 86).  Each
+// XCD takes a contiguous run of rows: 281 against 275 us.  A read of
+// the weights half a k-step ahead of the MFMAs, or two slots of rows in
+// flight instead of one, is slower (262 and 264 against 257 us).
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -34,8 +48,9 @@ typedef float sm_f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t sm_v4u32 __attribute__((ext_vector_type(4)));
 
 // LDS: two weight buffers [Cin][Cout] bf16 (32-byte column chunks XOR-
-// swizzled by row), srcs [K][R] int32, presence bytes [K][R/16], and one
-// epilogue staging tile [16][Cout + 8] bf16 per wavefront.
+// swizzled by row), which the epilogue's staging tiles [16][Cout + 8] bf16,
+// one per wavefront, replace after the last slot; srcs [K][R] int32 and
+// presence bytes [K][R/16].
 __host__ __device__ constexpr int sm_wbuf_bytes(int cin, int cout) { return cin * cout * 2; }
 __host__ __device__ constexpr int sm_stage_row(int cout) { return cout * 2 + 16; }
 // srcs [K][R] in row order, then sorted; perm [R]; per-slot counts and the
@@ -43,9 +58,17 @@ __host__ __device__ constexpr int sm_stage_row(int cout) { return cout * 2 + 16;
 __host__ __device__ inline int sm_idx_bytes(int K, int R) {
   return 4 * (2 * K * R + R + K + K + 2) + ((K * (R / 16) + 15) & ~15) + 16;
 }
+__host__ __device__ constexpr int sm_work_bytes(int cin, int cout, int nw) {
+  return 2 * sm_wbuf_bytes(cin, cout) > nw * 16 * sm_stage_row(cout)
+             ? 2 * sm_wbuf_bytes(cin, cout)
+             : nw * 16 * sm_stage_row(cout);
+}
 __host__ __device__ inline int sm_lds_bytes(int cin, int cout, int K, int R, int nw) {
-  return 2 * sm_wbuf_bytes(cin, cout) + ((sm_idx_bytes(K, R) + 15) & ~15) +
-         nw * 16 * sm_stage_row(cout);
+  return sm_work_bytes(cin, cout, nw) + ((sm_idx_bytes(K, R) + 15) & ~15);
+}
+// Two workgroups of 128 rows (whichever wavefronts) to a CU
+inline bool sm_two_per_cu(int cin, int cout, int K) {
+  return sm_lds_bytes(cin, cout, K, 128, 8) <= kSmLdsLimit / 2;
 }
 
 struct SmArgs {
@@ -61,13 +84,12 @@ struct SmArgs {
 
 // KS: 32-wide k-steps (Cin / 32); NCT: 16-column tiles (Cout / 16); NW:
 // wavefronts per workgroup; BPW: 16-row blocks per wavefront (R = 16 NW BPW
-// rows per workgroup); PD: slots of neighbour rows in flight ahead of the
-// one being multiplied; KF: K fixed at compile time (the slots fully
+// rows per workgroup); KF: K fixed at compile time (the slots fully
 // unrolled), or 0 for any K (a loop over the slots, whose back edge makes the
-// compiler wait for every load in flight); WSET: register sets of weights
-// (2: a slot's weights are loaded three slots ahead, 1: two).
-template <int KS, int NCT, int NW, int BPW, int PD, int KF, int WSET>
-__global__ __launch_bounds__(64 * NW, 1) void conv_sm_kernel(const SmArgs a) {
+// compiler wait for every load in flight); MINW: wavefronts per SIMD the
+// registers leave room for.
+template <int KS, int NCT, int NW, int BPW, int KF, int MINW>
+__global__ __launch_bounds__(64 * NW, MINW) void conv_sm_kernel(const SmArgs a) {
   constexpr int NT = 64 * NW;
   constexpr int Cin = KS * 32;
   constexpr int Cout = NCT * 16;
@@ -79,18 +101,17 @@ __global__ __launch_bounds__(64 * NW, 1) void conv_sm_kernel(const SmArgs a) {
   static_assert(WVEC % NT == 0, "whole weight vectors per thread");
   static_assert(R % 64 == 0, "a wavefront's 64 consecutive rows share a slot");
   constexpr int SROW = sm_stage_row(Cout);
-  constexpr int NSET = PD + 1;             // register sets of neighbour rows
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int K = KF > 0 ? KF : a.K;
   unsigned char* wbuf = smem;                                             // [2][Cin][WROW]
-  int32_t* srcs_in = reinterpret_cast<int32_t*>(smem + 2 * sm_wbuf_bytes(Cin, Cout));  // [K][R]
+  int32_t* srcs_in = reinterpret_cast<int32_t*>(smem + sm_work_bytes(Cin, Cout, NW));  // [K][R]
   int32_t* srcs = srcs_in + K * R;        // [K][R], sorted positions
   int32_t* perm = srcs + K * R;           // [R] sorted position -> row
   int32_t* cnt = perm + R;                // [K] rows present per slot
   int32_t* hist = cnt + K;                // [K + 2] bucket counts, then cursors
   uint8_t* pres = reinterpret_cast<uint8_t*>(hist + K + 2);  // [K][R/16]
-  unsigned char* stage = smem + 2 * sm_wbuf_bytes(Cin, Cout) + ((sm_idx_bytes(K, R) + 15) & ~15);
+  unsigned char* stage = smem;             // in place of wbuf, after the last slot
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -98,7 +119,7 @@ __global__ __launch_bounds__(64 * NW, 1) void conv_sm_kernel(const SmArgs a) {
   const int g = lane >> 4;
   const int l16 = lane & 15;
   const int64_t n = a.n_rows;
-  const int64_t row0 = (int64_t)blockIdx.x * R;
+  const int64_t row0 = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * R;
   const int nrows = (int)min((int64_t)R, n - row0);
 
   // ---- weights of a slot: global -> registers -> LDS.  The 32-byte column
@@ -112,18 +133,17 @@ __global__ __launch_bounds__(64 * NW, 1) void conv_sm_kernel(const SmArgs a) {
     else return ((r >> 1) & 1) | (((r >> 3) & 1) << 1);
   };
   const unsigned char* W = static_cast<const unsigned char*>(a.W);
-  // slot m's weights are loaded WSET + 1 slots ahead of use (register set
-  // m % WSET) and stored one slot ahead (buffer m & 1)
-  static_assert(WSET == 1 || WSET == 2, "one or two register sets of weights");
-  i32x4 wreg[WSET][NWV];
-  auto load_w = [&](int j, i32x4 (&wr)[NWV]) {
+  // slot m's weights are loaded two slots ahead of use and stored one slot
+  // ahead (buffer m & 1)
+  i32x4 wreg[NWV];
+  auto load_w = [&](int j) {
 #pragma unroll
     for (int u = 0; u < NWV; ++u) {
       const int v = u * NT + tid;
-      wr[u] = *reinterpret_cast<const i32x4*>(W + ((int64_t)j * Cin * Cout) * 2 + v * 16);
+      wreg[u] = *reinterpret_cast<const i32x4*>(W + ((int64_t)j * Cin * Cout) * 2 + v * 16);
     }
   };
-  auto store_w = [&](int buf, const i32x4 (&wr)[NWV]) {
+  auto store_w = [&](int buf) {
     unsigned char* base = wbuf + buf * sm_wbuf_bytes(Cin, Cout);
 #pragma unroll
     for (int u = 0; u < NWV; ++u) {
@@ -131,7 +151,7 @@ __global__ __launch_bounds__(64 * NW, 1) void conv_sm_kernel(const SmArgs a) {
       const int k = v / VPR;
       const int q = v - k * VPR;
       const int col = (((q >> 1) ^ swz_row(k)) << 5) + ((q & 1) << 4);
-      *reinterpret_cast<i32x4*>(base + k * WROW + col) = wr[u];
+      *reinterpret_cast<i32x4*>(base + k * WROW + col) = wreg[u];
     }
   };
   // B fragments of one k-step (rows 32 ks .. 32 ks + 31) from a buffer: two
@@ -154,7 +174,7 @@ __global__ __launch_bounds__(64 * NW, 1) void conv_sm_kernel(const SmArgs a) {
   };
 
   // ---- prologue: slot 0's weights on their way, then the table entries
-  load_w(0, wreg[0]);
+  load_w(0);
   for (int q = tid; q < 2 * K + 2; q += NT) cnt[q] = 0;  // cnt and hist
   __syncthreads();
   // entries (j, t) = (e / R, e % R): a wavefront reads 64 consecutive rows of
@@ -230,14 +250,14 @@ __global__ __launch_bounds__(64 * NW, 1) void conv_sm_kernel(const SmArgs a) {
     const uint64_t bal = __ballot(srcs[e] >= 0);
     if (l16 == 0) pres[(e / R) * (R / 16) + (e % R) / 16] = ((bal >> (lane & 48)) & 0xFFFFu) != 0;
   }
-  store_w(0, wreg[0]);
+  store_w(0);
   __syncthreads();
 
   // ---- neighbour rows of a slot for this wavefront's blocks: raw buffer
   // loads, an absent row reading zeros without touching memory
   const __amdgpu_buffer_rsrc_t s_rsrc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<void*>(a.S), (short)0, (int)(n * Cin * 2), kSmBufferWord3);
-  i32x4 areg[NSET][BPW][KS];
+  i32x4 areg[2][BPW][KS];
   auto issue_a = [&](int j, i32x4 (&dst)[BPW][KS]) {
 #pragma unroll
     for (int u = 0; u < BPW; ++u) {
@@ -262,25 +282,22 @@ __global__ __launch_bounds__(64 * NW, 1) void conv_sm_kernel(const SmArgs a) {
     for (int u = 0; u < BPW; ++u) acc[u][ct] = f32x4{b, b, b, b};
   }
 
-  // loads go out in the loop's own order (weights of slot m + 3 beside the
-  // rows of slot m + PD), so that every slot's waits count the same loads
-  static_assert(PD == 1 || PD == 2, "one or two slots of rows ahead");
+  // loads go out in the loop's own order (weights of slot m + 2 beside the
+  // rows of slot m + 1), so that every slot's waits count the same loads
   issue_a(0, areg[0]);
-  load_w(K > 1 ? 1 : K - 1, wreg[1 % WSET]);
-  if constexpr (PD == 2) issue_a(1, areg[1]);
-  if constexpr (WSET == 2) load_w(K > 2 ? 2 : K - 1, wreg[0]);
+  load_w(K > 1 ? 1 : K - 1);
 
-  // ---- the slots, in order; register set j % NSET, weight buffer j % 2
-  auto slot = [&](int j, i32x4 (&cur)[BPW][KS], i32x4 (&ahead)[BPW][KS], i32x4 (&wr)[NWV]) {
+  // ---- the slots, in order; register set and weight buffer j % 2
+  auto slot = [&](int j, i32x4 (&cur)[BPW][KS], i32x4 (&ahead)[BPW][KS]) {
     // slot j's weights were stored before this barrier; every wavefront is
-    // done with slot j - 1, so its buffer takes slot j + 1's (register set
-    // (j + 1) & 1, which then loads slot j + 3's).  Past the last slot the
-    // weights of slot K - 1 are loaded and stored again, into a buffer no
-    // slot reads any more, so that every slot issues the same loads.
+    // done with slot j - 1, so its buffer takes slot j + 1's, and their
+    // registers slot j + 2's.  Past the last slot the weights of slot K - 1
+    // are loaded and stored again, into a buffer no slot reads any more, so
+    // that every slot issues the same loads.
     __syncthreads();
-    store_w((j + 1) & 1, wr);
-    load_w(j + WSET + 1 < K ? j + WSET + 1 : K - 1, wr);
-    issue_a(j + PD, ahead);
+    store_w((j + 1) & 1);
+    load_w(j + 2 < K ? j + 2 : K - 1);
+    issue_a(j + 1, ahead);
     bool live[BPW];
     bool any = false;
 #pragma unroll
@@ -305,17 +322,14 @@ __global__ __launch_bounds__(64 * NW, 1) void conv_sm_kernel(const SmArgs a) {
   };
   if constexpr (KF > 0) {
 #pragma unroll
-    for (int j = 0; j < KF; ++j)
-      slot(j, areg[j % NSET], areg[(j + PD) % NSET], wreg[(j + 1) % WSET]);
+    for (int j = 0; j < KF; ++j) slot(j, areg[j & 1], areg[(j + 1) & 1]);
   } else {
-    // six slots per trip: register sets j % NSET and weight sets (j + 1) % 2
-    for (int j0 = 0; j0 < K; j0 += 6) {
-#pragma unroll
-      for (int p = 0; p < 6; ++p)
-        if (j0 + p < K)
-          slot(j0 + p, areg[p % NSET], areg[(p + PD) % NSET], wreg[(p + 1) % WSET]);
+    for (int j0 = 0; j0 < K; j0 += 2) {
+      slot(j0, areg[0], areg[1]);
+      if (j0 + 1 < K) slot(j0 + 1, areg[1], areg[0]);
     }
   }
+  __syncthreads();  // the staging tiles take the weights' place
 
   // ---- epilogue: act, bf16 (round to nearest even), staged per wavefront
   // so that every lane stores 16 contiguous bytes of a row
@@ -372,12 +386,10 @@ __global__ __launch_bounds__(64 * NW, 1) void conv_sm_kernel(const SmArgs a) {
   }
 }
 
-template <int KS, int NCT, int NW, int BPW, int PD, int KF>
+template <int KS, int NCT, int NW, int BPW, int KF, int MINW = 2>
 hipError_t launch_sm(const SmArgs& a, hipStream_t stream) {
   constexpr int R = BPW * 16 * NW;
-  // one wavefront per SIMD keeps five blocks' accumulators and rows in
-  // registers, with one register set of weights
-  auto kern = conv_sm_kernel<KS, NCT, NW, BPW, PD, KF, NW >= 8 ? 2 : 1>;
+  auto kern = conv_sm_kernel<KS, NCT, NW, BPW, KF, MINW>;
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [&] {
@@ -391,22 +403,34 @@ hipError_t launch_sm(const SmArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Rows per workgroup (one workgroup per CU: the LDS holds one): the fewest
-// of 128 (8 wavefronts x 1 block), 256 (8 x 2) and 320 (4 x 5, one
-// wavefront per SIMD holding all five blocks' accumulators and rows) that
-// covers the rows in one round, else 256 (nine slots) or 320.  The 8-wavefront
-// kernels run nine slots unrolled and two slots of rows ahead; the others
-// loop over the slots (whose back edge waits for every load, which with one
-// slot of rows ahead is about what the next slot waits for anyway).
+template <int KS, int NCT, int NW, int BPW>
+hipError_t launch_sm_k(const SmArgs& a, hipStream_t stream) {
+  // nine slots unrolled: 4 to 10% (236 against 247 us at 600,000 half-dense
+  // rows, 128 -> 128)
+  return a.K == 9 ? launch_sm<KS, NCT, NW, BPW, 9>(a, stream)
+                  : launch_sm<KS, NCT, NW, BPW, 0>(a, stream);
+}
+
+// 128 rows per workgroup where two fit a CU's LDS: eight wavefronts of one
+// block for 64 input channels, four of two blocks (a weight fragment read
+// feeds both) for 128, whose registers hold two wavefronts per SIMD either
+// way (128 -> 128 at 100,000 rows: 43 to 54 against 55 to 65 us with eight;
+// 64 -> 128: 24 to 30 with eight against 27 to 31), and for 64 -> 64 past the
+// rows the chip holds at once (300,000 rows, seven slots: 37 against 40 us,
+// at 80,000 13 against 14 the other way).  Else (128 -> 128 with 15 slots or
+// more) 320 rows: one wavefront per SIMD holding five blocks.
 template <int KS, int NCT>
 hipError_t launch_sm_rows(const SmArgs& a, int num_cus, hipStream_t stream) {
-  const int64_t n = a.n_rows;
-  const bool k9 = a.K == 9;
-  if ((n + 127) / 128 <= num_cus)
-    return k9 ? launch_sm<KS, NCT, 8, 1, 2, 9>(a, stream) : launch_sm<KS, NCT, 8, 1, 2, 0>(a, stream);
-  if (k9 && (n + 255) / 256 <= num_cus) return launch_sm<KS, NCT, 8, 2, 2, 9>(a, stream);
-  if ((n + 319) / 320 <= num_cus || !k9) return launch_sm<KS, NCT, 4, 5, 1, 0>(a, stream);
-  return launch_sm<KS, NCT, 8, 2, 2, 9>(a, stream);
+  if constexpr (KS == 4) {
+    if constexpr (NCT == 8)
+      if (!sm_two_per_cu(KS * 32, NCT * 16, a.K))
+        return launch_sm<KS, NCT, 4, 5, 0, 1>(a, stream);
+    return launch_sm_k<KS, NCT, 4, 2>(a, stream);
+  } else {
+    if constexpr (NCT == 4)
+      if (a.n_rows > 256LL * num_cus) return launch_sm_k<KS, NCT, 4, 2>(a, stream);
+    return launch_sm_k<KS, NCT, 8, 1>(a, stream);
+  }
 }
 
 }  // namespace
@@ -418,9 +442,11 @@ bool conv_sm_supported(const GemmArgs& a, bool bf16) {
   if (!((a.Cin == 64 || a.Cin == 128) && (a.Cout == 64 || a.Cout == 128))) return false;
   // 32-bit buffer offsets
   if (a.n_rows * a.Cin * 2 > 0x7FFF0000LL || a.n_rows * a.Cout * 2 > 0x7FFF0000LL) return false;
-  return sm_lds_bytes(a.Cin, a.Cout, a.K, 320, 4) <= kSmLdsLimit &&
-         sm_lds_bytes(a.Cin, a.Cout, a.K, 256, 8) <= kSmLdsLimit;
+  return sm_two_per_cu(a.Cin, a.Cout, a.K) ||
+         sm_lds_bytes(a.Cin, a.Cout, a.K, 320, 4) <= kSmLdsLimit;
 }
+
+bool conv_sm_two(const GemmArgs& a) { return sm_two_per_cu(a.Cin, a.Cout, a.K); }
 
 hipError_t launch_conv_sm(const GemmArgs& g, int num_cus, hipStream_t stream) {
   SmArgs a;

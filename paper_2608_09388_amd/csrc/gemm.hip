@@ -626,13 +626,24 @@ hipError_t launch_gather_gemm(const GemmArgs& a, bool conv, bool bf16, hipStream
   if (e != hipSuccess) return e;
   // The slot-major conv (every output column per workgroup, the slots in
   // turn) against the weight-stationary one (column slices of W resident,
-  // jobs of 16 rows x slot), measured at K = 9 (the same results bit for
-  // bit): faster from about 1000 rows per CU (the density-sweep batch at
-  // 20 / 50 / 100%: 112 / 282 / 612 us against 138 / 347 / 659 us; the
-  // full-mesh cap at 64 channels 54 against 95 us) and for 64 input
-  // channels within one round of 128-row groups (6.6 against 10.6 us at
-  // 4,200 rows); slower for 128 input channels at a few hundred rows per CU
-  // (36 against 26 us at 5% of the density-sweep batch).
+  // jobs of 16 rows x slot), the same results bit for bit:
+  //   * where the latter does not run (more than one wave of workgroups or ten
+  //     slots): nine slots, 100,000 rows at 10%, 128 -> 128 47 against 63 us
+  //     for the slot-walking kernel; 200,000 at 5%, 64 -> 128 39 against 80,
+  //     128 -> 64 44 against 60; thirteen slots, 130,000 rows, 64 -> 64 25
+  //     against 33, 128 -> 128 65 against 89;
+  //   * from 1000 rows per CU, where the sparse jobs' cost grows with the
+  //     density (270,000 rows at 30%, 64 -> 64: 36 against 50 us).  Below, the
+  //     density, which the host does not know, decides (nine slots, 100,000
+  //     rows, 64 -> 128: 23.2 against 20.2 us at 2%, 30 against 42 at 40%), and
+  //     the weight-stationary kernel keeps the sparse masks;
+  //   * for 64 input channels also within two 128-row workgroups per CU (nine
+  //     slots: 6.6 against 10.6 us at 4,200 rows, 9.5 against 13.1 at 65,000
+  //     and 2%, 64 -> 128 13.9 against 16.8), where only 64 -> 64 at five slots
+  //     comes near (9.9 against 12.3);
+  //   * where its workgroups fit one to a CU (128 -> 128, 15 slots and more),
+  //     from 1000 rows per CU (24 slots, 50,000 rows: 78 against 71 us for the
+  //     slot-walking kernel, 300,000: 255 against 257).
   // The slot-walking conv (conv_walk.hip) against both, the same bits:
   //   * bf16 64 -> 128 channels: 8.8 / 8.7 / 9.0 us at 2,000 / 4,000 / 8,000
   //     rows against 9.6 / 9.9 / 9.9 for the slot-major kernel, while its 128 x
@@ -650,14 +661,17 @@ hipError_t launch_gather_gemm(const GemmArgs& a, bool conv, bool bf16, hipStream
   if (walk && bf16 && a.Cin == 64 && a.Cout == 128 && conv_sm_supported(a, bf16) &&
       conv_walk_medium(a, cus, 1))
     return launch_conv_walk(a, bf16, false, cus, stream);
+  WsPlan plan;
+  const bool ws = ws_plan(a, conv, bf16, cus, &plan);
   if (conv && conv_sm_supported(a, bf16) &&
-      (a.n_rows >= 1000LL * cus || (a.Cin == 64 && a.n_rows <= 128LL * cus)))
+      (a.n_rows >= 1000LL * cus ||
+       (conv_sm_two(a) && (a.Cin == 64 ? a.n_rows <= 256LL * cus || !ws
+                                       : a.n_rows > 128LL * cus && !ws))))
     return launch_conv_sm(a, cus, stream);
   if (walk && !bf16 &&
       (conv_walk_small(a, cus) || (a.K * a.Cin <= 288 && conv_walk_medium(a, cus, 2))))
     return launch_conv_walk(a, bf16, false, cus, stream);
-  WsPlan plan;
-  if (ws_plan(a, conv, bf16, cus, &plan)) return launch_ws_gemm(a, conv, bf16, plan, stream);
+  if (ws) return launch_ws_gemm(a, conv, bf16, plan, stream);
   // a conv plan exists only for the weight-stationary kernel
   if (a.plan != nullptr || a.plan_out != nullptr) return hipErrorInvalidValue;
   if (walk) {

@@ -35,6 +35,14 @@ __device__ __forceinline__ T ceil_div(T a, T b) {
   return (a + b - 1) / b;
 }
 
+// Tile of workgroup b of n.  Workgroups are dealt to the eight XCDs in turn
+// (b runs on XCD b % 8); each XCD takes a contiguous range of tiles, so that
+// rows that neighbouring tiles both read stay in its L2.
+__device__ __forceinline__ int xcd_tile(int b, int n) {
+  const int x = b & 7, q = n >> 3, r = n & 7;
+  return x * q + (x < r ? x : r) + (b >> 3);
+}
+
 // ---------------------------------------------------------------------------
 // launchers (host side, enqueue only; arguments already validated)
 // ---------------------------------------------------------------------------
@@ -194,6 +202,7 @@ hipError_t launch_conv_walk(const GemmArgs& a, bool bf16, bool split, int num_cu
 // slot-major conv from a neighbour-row table (conv_sm.hip): bf16, C_in and
 // C_out in {64, 128}, K <= 32, no plan
 bool conv_sm_supported(const GemmArgs& a, bool bf16);
+bool conv_sm_two(const GemmArgs& a);  // its workgroups fit two to a CU
 hipError_t launch_conv_sm(const GemmArgs& a, int num_cus, hipStream_t stream);
 // conv from a neighbour-row table with slot 0 and the other slots apart
 // (conv_split.hip): bf16, C_in and C_out in {64, 128, 256}, K <= 32; the

@@ -71,3 +71,37 @@ def test_conv_sm_shapes_against_oracle(dev, B, V, K, Cin, Cout, p, mesh):
         assert_scaled_close(got[rows], ref, scale, "bf16",
                             f"conv K={K} {Cin}->{Cout} p={p} act={act}", n_terms=K * Cin)
     torch.cuda.synchronize()
+
+
+# 128-row workgroups, two to a CU, their output staged where the weights were:
+# eight wavefronts and four, a last group that is nearly empty, one and two
+# slots (the staging tiles then reach past the weights), an odd and an even
+# slot count of the loop, and the 320-row form where two do not fit; rows past
+# N' untouched.
+@pytest.mark.parametrize("n,K,Cin,Cout", [
+    (129, 1, 64, 128), (2 * 128 + 1, 2, 64, 64), (65536, 5, 64, 64), (65537, 9, 64, 64),
+    (65537, 6, 64, 64), (40001, 12, 128, 64), (32769, 11, 128, 128), (32900, 14, 128, 128),
+    (256000, 9, 128, 64), (256003, 15, 128, 128),
+])
+def test_conv_sm_workgroups_against_dense_products(dev, n, K, Cin, Cout):
+    g = torch.Generator(device=dev).manual_seed(n + K)
+    table = torch.randint(0, n, (K, n), generator=g, device=dev, dtype=torch.int32)
+    table[torch.rand((K, n), generator=g, device=dev) < 0.6] = -1
+    S = torch.randn((n, Cin), generator=g, device=dev).to(torch.bfloat16)
+    W = (torch.randn((K, Cin, Cout), generator=g, device=dev) / (K * Cin) ** 0.5).to(torch.bfloat16)
+    bias = torch.randn(Cout, generator=g, device=dev)
+    out = torch.full((n + 1, Cout), float("nan"), dtype=torch.bfloat16, device=dev)
+    shc.sparse_neighbor_conv_table(S, table, n, W, bias, out, shc.SHC_ACT_RELU)
+    rows = torch.cat([torch.arange(min(n, 300)), torch.arange(max(0, n - 300), n),
+                      torch.arange(0, n, max(1, n // 500))]).to(dev)
+    ref = bias.double().expand(len(rows), Cout).clone()
+    scale = ref.abs()
+    for j in range(K):
+        src = table[j][rows].long()
+        x = torch.where((src >= 0)[:, None], S[src.clamp(min=0)], torch.zeros_like(S[:1])).double()
+        ref += x @ W[j].double()
+        scale += x.abs() @ W[j].double().abs()
+    assert torch.isnan(out[n:]).all()
+    assert_scaled_close(out[rows].float().cpu().numpy(), ref.clamp(min=0).cpu().numpy(),
+                        scale.cpu().numpy(), "bf16", f"conv n={n} K={K} {Cin}->{Cout}",
+                        n_terms=K * Cin)
