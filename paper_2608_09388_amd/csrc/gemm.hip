@@ -14,6 +14,11 @@
 // the per-output index list r_i. is the paper's indexing matrix (Eq. 4)
 // evaluated on the fly.
 //
+// This file holds the tiled kernel, which runs linear layers of large shapes,
+// large bf16 convs of wide outputs or few slots, and convs whose buffers need
+// 64-bit offsets, and the dispatch over it and
+// the other conv and linear kernels (launch_gather_gemm).
+//
 // Tiling (one workgroup = 4 wavefronts = 256 threads):
 //   * a tile of BM = 128 active rows x BN (64 or 128) output channels; tiles
 //     are handed out so that each XCD works on a contiguous range of rows
@@ -656,7 +661,17 @@ hipError_t launch_gather_gemm(const GemmArgs& a, bool conv, bool bf16, hipStream
   //     slower at few reduction entries (16 channels, 15,851 rows: 10.4
   //     against 19.2 us; 32 channels: 12.3 against 14.6), up to 32 a slot at
   //     K = 9;
-  //   * everything the weight-stationary kernel does not take.
+  //   * what neither takes, but for sets of more than 128 rows per CU in bf16
+  //     with whole 128-column tiles, which the tiled kernel gathers once where
+  //     the walk gathers per 64 columns (270,000 rows, nine slots: 64 -> 256
+  //     134 against 196 us, 128 -> 256 217 against 263, 256 -> 256 388 against
+  //     401; 256 -> 64 161 against 117 the other way, 192 -> 192 301 against
+  //     252), or with few slots to pay for the index prologue (500,000 rows,
+  //     seven slots: 48 -> 80 123 against 145 us, 32 -> 64 56 against 69; at
+  //     31,000 rows 16 against 13); and short reductions into more than 64 columns
+  //     from 64 rows per CU (nine slots, 16 -> 256: 25,000 bf16 rows 15 against
+  //     20 us, 8,000 12 against 9; 200,000 fp32 rows 139 against 178; 16 -> 96:
+  //     40,000 bf16 rows 12.8 against 15.1).
   const bool walk = conv && conv_walk_supported(a, bf16);
   if (walk && bf16 && a.Cin == 64 && a.Cout == 128 && conv_sm_supported(a, bf16) &&
       conv_walk_medium(a, cus, 1))
@@ -674,7 +689,11 @@ hipError_t launch_gather_gemm(const GemmArgs& a, bool conv, bool bf16, hipStream
   if (ws) return launch_ws_gemm(a, conv, bf16, plan, stream);
   // a conv plan exists only for the weight-stationary kernel
   if (a.plan != nullptr || a.plan_out != nullptr) return hipErrorInvalidValue;
-  if (walk) {
+  const bool brief = a.K * a.Cin < 256;
+  const bool tile = (brief && a.Cout > 64 && a.n_rows > 64LL * cus) ||
+                    (bf16 && a.n_rows > 128LL * cus &&
+                     (a.Cout % 128 == 0 || a.K < 9 || brief));
+  if (walk && !tile) {
     // fp32 products split into bf16 ones only where no other kernel runs the
     // shape from a table either (a conv from coordinates leaves the
     // weight-stationary kernel by density), so that a conv gives the same bits
@@ -683,7 +702,6 @@ hipError_t launch_gather_gemm(const GemmArgs& a, bool conv, bool bf16, hipStream
     t.table = static_cast<const int32_t*>(a.S);  // (only its presence is read)
     return launch_conv_walk(a, bf16, !ws_plan(t, conv, bf16, cus, &plan), cus, stream);
   }
-  // the linear layer, and convs whose buffers need 64-bit offsets
   if (bf16) return conv ? launch_typed<true, true>(a, stream) : launch_typed<true, false>(a, stream);
   return conv ? launch_typed<false, true>(a, stream) : launch_typed<false, false>(a, stream);
 }
