@@ -9,9 +9,8 @@
 // by them, and slot j + 1's weights are loaded beside that work into the
 // other of two buffers; the neighbour rows of slot j + 1 are in flight in
 // registers meanwhile.  Each gathered row therefore feeds all Cout
-// columns at once, and the index work per row group is one pass over its
-// table entries (no sort, no job lists).  A (16-row block, slot) pair with
-// no present row is skipped.  Accumulation is in fp32, per output element
+// columns at once.  Rows are sorted by their first sparse slot, and a (16-row
+// block, slot) pair with no present row is skipped.  Accumulation is in fp32, per output element
 // in slot order and within a slot in k order.
 //
 // What bounds it: a slot's weight reads from LDS and its MFMAs take about as
