@@ -119,8 +119,10 @@ __device__ __forceinline__ void split3(walk_v2u32 x, uint32_t* h, uint32_t* m, u
 // thread's weights of one have their largest magnitude in these ranges (or are
 // all zero): below 2^-100 the third terms would leave bf16's range, and the
 // upper limits keep every product and partial sum of the terms finite where
-// the fp32 product is.  A wavefront that meets others computes its rows again
-// on the fp32 matrix cores.
+// the fp32 product is.  Rows that use other input values, and every row of a
+// workgroup that meets other weights, are computed again on the fp32 matrix
+// cores; the rows beside them in a wavefront keep their split sums (the order
+// of rows inside a sort bucket differs from launch to launch).
 constexpr float kSplitMin = 0x1p-100f;
 constexpr float kSplitMaxA = 0x1p96f;
 constexpr float kSplitMaxW = 0x1p24f;
@@ -300,7 +302,7 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
     // rows sorted by their first sparse slot (one present in fewer than half
     // of the rows): bucket 0 has dense slots only, 1 + j first sparse slot j,
     // K + 1 is past the last row.  The order inside a bucket is whatever the
-    // atomics give, which no result depends on.
+    // atomics give, which no result depends on: a row's sums are its own.
     constexpr int RPT = (R + NT - 1) / NT;
     int bkt[RPT];
     uint32_t rm[RPT];
@@ -559,8 +561,16 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
   }
 
   if constexpr (SPLIT) {
-    if (__builtin_amdgcn_readfirstlane(*w_wild) != 0 || __ballot(wild) != 0) {
-      // this wavefront's rows again on the fp32 matrix cores, straight from memory
+    // a lane's accumulators are row l16's, whose entries its four lane groups hold
+    int out_of_range = (wild ? 1 : 0) | *w_wild;
+    out_of_range |= __shfl_xor(out_of_range, 16, 64);
+    out_of_range |= __shfl_xor(out_of_range, 32, 64);
+    const bool redo = out_of_range != 0;
+    if (__ballot(redo) != 0) {
+      // the wavefront's rows again on the fp32 matrix cores, straight from memory
+      f32x4 kept[NCT];
+#pragma unroll
+      for (int ct = 0; ct < NCT; ++ct) kept[ct] = acc[ct];
       init_acc();
 #pragma unroll 1
       for (int s = 0; s < nks; ++s) {
@@ -588,6 +598,14 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
           }
         }
       }
+      // the last MFMAs may sit right behind the loop's branch (see below)
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[ct][i] = redo ? acc[ct][i] : kept[ct][i];
     }
   }
 

@@ -129,3 +129,62 @@ def test_conv_walk_value_range(dev, what):
     # 1e-5 of the abs-sum scale, and the spacing of fp32's smallest numbers for
     # each of the K Cin products and sums below its normal range
     assert np.all(np.abs(got[ok] - ref[ok]) <= 1e-5 * scale[ok] + 2 * K * Cin * 2.0 ** -149)
+
+
+def split_problem(dev, n, K, Cin, Cout, seed, keep=1.0):
+    """Bodies, lists, table and values of a shape whose fp32 products are split
+    (on the GPU); features are post-activation values, `keep` of them nonzero."""
+    g = torch.Generator(device=dev).manual_seed(seed)
+    B, V = 64, (n + 31) // 32
+    nbr = torch.randint(0, V, (V, K), generator=g, device=dev, dtype=torch.int32)
+    nbr[:, 0] = torch.arange(V, device=dev)
+    m = np.zeros(B * V, dtype=np.uint8)
+    m[np.random.default_rng(seed).permutation(B * V)[:n]] = 1
+    c = Compaction(m.reshape(B, V))
+    assert c.run() == n
+    S = torch.randn((n, Cin), generator=g, device=dev).abs()
+    S *= torch.rand((n, Cin), generator=g, device=dev) < keep
+    W = torch.randn((K, Cin, Cout), generator=g, device=dev) / (K * Cin) ** 0.5
+    table = torch.empty(K * n, dtype=torch.int32, device=dev)
+    shc.build_neighbor_table(c.coords, c.inv, n, B, V, nbr, table)
+
+    def conv(S, W, bias=None, coords=False):
+        out = torch.full((n, Cout), float("nan"), device=dev)
+        if coords:
+            shc.sparse_neighbor_conv(S, c.coords, c.inv, n, B, V, nbr, W, bias, out,
+                                     shc.SHC_ACT_NONE)
+        else:
+            shc.sparse_neighbor_conv_table(S, table, n, W, bias, out, shc.SHC_ACT_NONE)
+        return out
+
+    return S, W, table.view(K, n), conv
+
+
+def bits(t):
+    """int32 view with one NaN pattern."""
+    return torch.where(torch.isnan(t), torch.full_like(t, float("nan")), t).view(torch.int32)
+
+
+@pytest.mark.parametrize("n", [17001, 33500])  # 256- and 128-row workgroups
+@pytest.mark.parametrize("what", ["infinite", "huge", "tiny"])
+def test_conv_walk_split_rows_apart(dev, n, what):
+    """Values outside the split's range change the sums of the rows that use
+    them and of no other: rows that do not have the same bits as without them,
+    in every launch and from coordinates, whichever rows share a wavefront."""
+    S, W, table, conv = split_problem(dev, n, 9, 128, 128, n)
+    plain = conv(S, W)
+    odd = torch.zeros(n, dtype=torch.bool, device=dev)
+    odd[torch.from_numpy(np.random.default_rng(n).choice(n, 40, replace=False)).to(dev)] = True
+    T = S.clone()
+    if what == "infinite":
+        T[odd, 3] = float("inf")
+    elif what == "huge":
+        T[odd] *= 2.0 ** 100
+    else:
+        T[odd] *= 2.0 ** -110
+    uses = ((table >= 0) & odd[table.clamp(min=0).long()]).any(0)
+    assert 0 < int(uses.sum()) < n // 2
+    got = conv(T, W)
+    assert torch.equal(bits(got)[~uses], bits(plain)[~uses])
+    for coords in (False, True, False, True):
+        assert torch.equal(bits(conv(T, W, coords=coords)), bits(got))
