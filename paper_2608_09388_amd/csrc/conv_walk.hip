@@ -96,13 +96,9 @@ __host__ __device__ constexpr int walk_idx_bytes(int K, int R, bool sorted) {
 }
 
 // A pair of fp32 values as three bf16 pairs, x = h + m + l exactly: each term
-// is the nearest bf16 to what is left, 8 + 8 + 8 significand bits.  *big takes
-// the larger magnitude (a NaN is ignored: it stays one in h and in every
-// product, as in fp32).
-__device__ __forceinline__ void split3(walk_v2u32 x, uint32_t* h, uint32_t* m, uint32_t* l,
-                                       float* big) {
+// is the nearest bf16 to what is left, 8 + 8 + 8 significand bits.
+__device__ __forceinline__ void split3(walk_v2u32 x, uint32_t* h, uint32_t* m, uint32_t* l) {
   const float x0 = __uint_as_float(x[0]), x1 = __uint_as_float(x[1]);
-  *big = fmaxf(fmaxf(*big, fabsf(x0)), fabsf(x1));
   const uint32_t hh = __builtin_bit_cast(
       uint32_t, __builtin_convertvector(walk_f32x2{x0, x1}, walk_bf16x2));
   const float r0 = x0 - __uint_as_float(hh << 16), r1 = x1 - __uint_as_float(hh & 0xFFFF0000u);
@@ -115,17 +111,30 @@ __device__ __forceinline__ void split3(walk_v2u32 x, uint32_t* h, uint32_t* m, u
                           __builtin_convertvector(walk_f32x2{s0, s1}, walk_bf16x2));
 }
 
-// The split product is used while a lane's 16 input values of a phase and a
-// thread's weights of one have their largest magnitude in these ranges (or are
-// all zero): below 2^-100 the third terms would leave bf16's range, and the
-// upper limits keep every product and partial sum of the terms finite where
-// the fp32 product is.  Rows that use other input values, and every row of a
-// workgroup that meets other weights, are computed again on the fp32 matrix
-// cores; the rows beside them in a wavefront keep their split sums (the order
-// of rows inside a sort bucket differs from launch to launch).
+// The split product is used for values that are zero or in these ranges: below
+// 2^-100 the third terms would leave bf16's range, and the upper limits keep
+// every product and partial sum of the terms finite where the fp32 product is.
+// (A NaN stays one in h and in every product, as in fp32.)  Rows that use
+// other input values, and every row of a workgroup that meets other weights,
+// are computed again on the fp32 matrix cores; the rows beside them in a
+// wavefront keep their split sums (the order of rows inside a sort bucket
+// differs from launch to launch).
 constexpr float kSplitMin = 0x1p-100f;
 constexpr float kSplitMaxA = 0x1p96f;
 constexpr float kSplitMaxW = 0x1p24f;
+
+// The smallest and largest magnitude of the values seen.
+struct SplitRange {
+  uint32_t small = 0xFFFFFFFFu;  // 2 |bits| - 1: a zero is the largest
+  float big = 0.f;               // (ignores a NaN)
+  __device__ __forceinline__ void see(int x) {
+    small = min(small, ((uint32_t)x << 1) - 1u);
+    big = fmaxf(big, fabsf(__int_as_float(x)));
+  }
+  __device__ __forceinline__ bool outside(float max) const {
+    return small < (__builtin_bit_cast(uint32_t, kSplitMin) << 1) - 1u || !(big < max);
+  }
+};
 
 // NA: register sets of input rows (NA - 1 phases in flight); NWS: register
 // sets of weights; MINW: wavefronts per SIMD that the registers must allow.
@@ -212,7 +221,7 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
   };
   auto store_w = [&](int buf, const i32x4 (&wv)[NWV]) {
     unsigned char* base = smem + buf * WBUF;
-    float big = 0.f;
+    SplitRange seen;
 #pragma unroll
     for (int u = 0; u < NWV; ++u) {
       const int v = u * NT + tid;
@@ -224,8 +233,10 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
         const walk_v2u32 x = {(uint32_t)wv[u][0], (uint32_t)wv[u][1]};
         const walk_v2u32 y = {(uint32_t)wv[u][2], (uint32_t)wv[u][3]};
         uint32_t h0, m0, l0, h1, m1, l1;
-        split3(x, &h0, &m0, &l0, &big);
-        split3(y, &h1, &m1, &l1, &big);
+        split3(x, &h0, &m0, &l0);
+        split3(y, &h1, &m1, &l1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) seen.see(wv[u][i]);
         unsigned char* p = base + k * WROW + col;
         *reinterpret_cast<walk_v2u32*>(p) = walk_v2u32{h0, h1};
         *reinterpret_cast<walk_v2u32*>(p + WPL) = walk_v2u32{m0, m1};
@@ -236,7 +247,7 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
       }
     }
     if constexpr (SPLIT) {
-      if (!(big == 0.f || (big >= kSplitMin && big < kSplitMaxW))) *w_wild = 1;
+      if (seen.outside(kSplitMaxW)) *w_wild = 1;
     }
   };
   i32x4 wreg[NWS][NWV];
@@ -487,12 +498,12 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
     if (!live) return;
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (SPLIT) {
-      float big = 0.f;  // the lane's largest input magnitude
+      SplitRange seen;
 #pragma unroll
       for (int ks = 0; ks < kPhaseSteps; ++ks)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) big = fmaxf(big, fabsf(__int_as_float(cur[ks][i])));
-      wild = wild || !(big == 0.f || (big >= kSplitMin && big < kSplitMaxA));
+        for (int i = 0; i < 4; ++i) seen.see(cur[ks][i]);
+      wild = wild || seen.outside(kSplitMaxA);
       // two k-steps of 32 entries; lane group g holds entries 4g .. 4g+3 of
       // each of their two 16-entry halves.  Stage (m, plane): the plane's
       // weights by every input term that with it makes a product above 2^-24
@@ -508,8 +519,7 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
             const i32x4& v = cur[2 * m + q / 2];
             const walk_v2u32 x = {(uint32_t)v[2 * (q & 1)], (uint32_t)v[2 * (q & 1) + 1]};
             uint32_t h, mm, l;
-            float unused = 0.f;
-            split3(x, &h, &mm, &l, &unused);
+            split3(x, &h, &mm, &l);
             t[0][q] = h;
             t[1][q] = mm;
             t[2][q] = l;

@@ -160,6 +160,20 @@ def split_problem(dev, n, K, Cin, Cout, seed, keep=1.0):
     return S, W, table.view(K, n), conv
 
 
+def dense_products(S, W, table, bias=None):
+    """The conv and its sum of absolute products in 64 bits."""
+    ref = torch.zeros((S.shape[0], W.shape[2]), dtype=torch.float64, device=S.device)
+    if bias is not None:
+        ref += bias.double()
+    scale = ref.abs()
+    for j in range(W.shape[0]):
+        r = table[j].long()
+        x = S.double()[r.clamp(min=0)] * (r >= 0)[:, None]
+        ref += x @ W[j].double()
+        scale += x.abs() @ W[j].double().abs()
+    return ref, scale
+
+
 def bits(t):
     """int32 view with one NaN pattern."""
     return torch.where(torch.isnan(t), torch.full_like(t, float("nan")), t).view(torch.int32)
@@ -188,3 +202,31 @@ def test_conv_walk_split_rows_apart(dev, n, what):
     assert torch.equal(bits(got)[~uses], bits(plain)[~uses])
     for coords in (False, True, False, True):
         assert torch.equal(bits(conv(T, W, coords=coords)), bits(got))
+
+
+@pytest.mark.parametrize("what", ["weight column", "input channel", "products"])
+def test_conv_walk_split_mixed_magnitudes(dev, what):
+    """Tiny values beside ordinary ones keep their precision: a weight column of
+    2^-120 among ordinary columns, an input channel of 2^-120 whose neighbours
+    meet zero weights, and products near the smallest normal number.  Against
+    64 bits relative to each output's sum of absolute products: fp32 sums of
+    K Cin terms err by less than K Cin 2^-24 of it, and by 2^-149 an operation
+    below fp32's normal range."""
+    n, K, Cin, Cout = 17001, 9, 128, 128
+    S, W, table, conv = split_problem(dev, n, K, Cin, Cout, 5)
+    if what == "weight column":
+        W[:, :, 17] *= 2.0 ** -120
+    elif what == "input channel":
+        S[:, 5] *= 2.0 ** -120
+        W[:, :5] = 0
+        W[:, 6:] = 0
+        W[:, 5] *= 2.0 ** 20
+    else:
+        S *= 2.0 ** -60
+        W *= 2.0 ** -62
+    ref, scale = dense_products(S, W, table)
+    err = (conv(S, W).double() - ref).abs()
+    # a random walk of the roundings: 4e-7 seen, 1e-6 of the scale allowed (a
+    # value kept to 16 bits errs by 2^-17 = 7.6e-6)
+    assert bool((err <= 1e-6 * scale + 2 * K * Cin * 2.0 ** -149).all()), \
+        float((err / scale.clamp(min=1e-300)).max())
