@@ -270,6 +270,14 @@ int shc_gather_sparse_linear(const void* x, const int32_t* coords, int64_t n_row
  *   bias    [Cout] fp32 or NULL.   K in [1, 32].
  *   out     [n_rows][Cout], must not overlap S.
  * n_rows = 0 is a no-op.
+ * Sums are in fp32.  fp32 convs of many rows form their products from three
+ * bf16 terms a value (six of the nine products of terms, the large one summed
+ * apart from the others) where no weight is infinite, 2^24 or more or, unless
+ * zero, under 2^-100, and for the rows whose input values are below 2^96 and,
+ * unless zero, not under 2^-100; the error against exact sums is no larger
+ * than the fp32 matrix cores', which take every other row.  Which form a shape
+ * takes follows n_rows, so the last bits of a row's result may differ between
+ * calls of different n_rows; calls of the same arguments give the same bits.
  */
 int shc_sparse_neighbor_conv(const void* S, const int32_t* coords, const int32_t* inv,
                              int64_t n_rows, int32_t B, int32_t V, const int32_t* nbr, int32_t K,

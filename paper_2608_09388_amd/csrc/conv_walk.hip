@@ -28,16 +28,25 @@
 // conv kernels: where they run the same shape the results are the same bits
 // (but for the split below).
 //
-// fp32 in the largest workgroups takes each product as six bf16 ones (SPLIT):
-// an fp32 value is three bf16 terms h + m + l exactly (8 + 8 + 8 significand
-// bits), the products h h, h m, m h, m m, h l and l h are exact in fp32 and are
-// summed there, and what is left out (m l, l m, l l) is below 2^-24 of a
-// product.  Six 16-bit MFMAs of 32 entries take 96 cycles, eight fp32 ones 256.
-// The sums have fewer roundings than the fp32 chain (six a 32-entry k-step
-// instead of eight): 2-norm error against 64 bits 3.7e-7 instead of 4.3e-7 at
-// K Cin = 576 (cap mask), 3.3e-7 instead of 3.8e-7 at 1,152, 1.3e-7 instead of
-// 1.5e-7 at 288.  The rows' terms are formed in registers, the weights' as they
-// are stored to LDS (three planes).
+// fp32 in the largest workgroups takes each product as six bf16 ones (SPLIT; the
+// three-term splitting is that of Henry, Tang and Heinecke, "Leveraging the
+// bfloat16 artificial intelligence datatype for higher-precision
+// computations", 2019): an fp32 value is three bf16 terms h + m + l exactly
+// (8 + 8 + 8 significand bits), and the products h h, h m, m h, m m, h l and
+// l h are exact in fp32.  Left out are m l, l m and l l, together at most 2^-23
+// of a product (root mean square about 2^-27; the rounding of an fp32 sum is
+// up to 2^-24 of the sum).  The h h products are summed in one accumulator, the
+// others, at most 2^-7 of them, in a second; the two and the bias are added in
+// fp64 and rounded once.  So a 32-entry k-step rounds the large sum once, where the fp32 matrix
+// cores round it for each of its four-entry groups with a nonzero product, and
+// the 2-norm error against 64 bits is below theirs from dense features to two
+// nonzero products an output (128 -> 128, nine slots half present, fp32 matrix
+// cores / split: dense 4.7e-7 / 1.5e-7, half of the features nonzero 3.3e-7 /
+// 1.2e-7, a tenth 1.5e-7 / 5.8e-8, 0.4% 3.9e-8 / 2.6e-8; with all six products
+// in one accumulator the split erred by 3.9e-7, 2.7e-7 and 8.4e-8 on the last
+// three).  Six 16-bit MFMAs of 32 entries take 96 cycles, eight fp32 ones 256.
+// The rows' terms are formed in registers, the weights' as they are stored to
+// LDS (three planes).
 //
 // What bounds it.  Few rows: the chain of phases, each about 0.6 us (barrier,
 // LDS write to read, a dependent MFMA chain), so 16-row workgroups spread over
@@ -45,10 +54,11 @@
 // of the weight-stationary kernel, 6.9 us here; 1,965 rows 128 -> 128 fp32:
 // 96 -> 18.6 us; 1,965 rows bf16 256 -> 256: 56 -> 15.8 us).  Many rows in
 // fp32: the fp32 matrix rate held it at 370 us for 499 K rows 64 -> 64 with
-// 0.91 of the slots present (400 us in the tiled kernel); split, 279 us, bound
+// 0.91 of the slots present (400 us in the tiled kernel); split, 295 us, bound
 // by the VALU work of the split, the LDS reads of three planes and the MFMAs
 // at about equal shares, and the index prologue of every workgroup (32 K rows
-// 128 -> 128: 117, 84 and 53 us; 26 K rows 256 -> 256: 259, 222 and 160 us).
+// 128 -> 128: 117, 84 and 59 us; 26 K rows 256 -> 256: 259, 222 and 175 us;
+// with all products in one accumulator 282, 58 and 161 us).
 // Many rows in bf16: the weight stage per 128 rows (93 K rows, K = 5, 32 -> 80:
 // 30 -> 26 us; 19 K rows, K = 7, 48 -> 80 from coordinates: 16.2 -> 11.7 us).
 #include <mutex>
@@ -397,20 +407,22 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
   // 4 P consecutive columns
   const int cbase = n0 + wc * NCT * 16 + 4 * P * g;
   auto col_of = [&](int ct, int r) -> int { return cbase + (ct / P) * 16 * P + P * r + ct % P; };
-  // accumulators start at the bias of their columns (row l16 of a block)
-  f32x4 acc[NCT];
-  auto init_acc = [&]() {
+  // accumulators start at the bias of their columns (row l16 of a block), the
+  // split's at zero: its bias joins where the two sums do
+  f32x4 acc[NCT], low[SPLIT ? NCT : 1];
+  auto bias_of = [&](int ct) -> f32x4 {
+    f32x4 b = {0.f, 0.f, 0.f, 0.f};
+    if (a.bias != nullptr) {
 #pragma unroll
-    for (int ct = 0; ct < NCT; ++ct) {
-      f32x4 b = {0.f, 0.f, 0.f, 0.f};
-      if (a.bias != nullptr) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) b[r] = col_of(ct, r) < Cout ? a.bias[col_of(ct, r)] : 0.f;
-      }
-      acc[ct] = b;
+      for (int r = 0; r < 4; ++r) b[r] = col_of(ct, r) < Cout ? a.bias[col_of(ct, r)] : 0.f;
     }
+    return b;
   };
-  init_acc();
+#pragma unroll
+  for (int ct = 0; ct < NCT; ++ct) {
+    if constexpr (SPLIT) acc[ct] = low[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+    else acc[ct] = bias_of(ct);
+  }
 
   i32x4 areg[NA][kPhaseSteps];
   uint32_t off[kPhaseSteps];  // of the phase whose loads go out next
@@ -455,21 +467,24 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
       }
     }
   };
-  // split weights: plane st % 3 of the 32-entry k-step st / 3, entries
-  // 4g .. 4g+3 of both its halves for column i
-  auto read_plane = [&](const unsigned char* base, int st, WFrag& f) {
-    const int r = 32 * (st / 3) + 4 * g + (l16 >> 2);
+  // split weights: the three planes of column tile ct of the 32-entry k-step
+  // m, entries 4g .. 4g+3 of both its halves for column i
+  struct WPlanes {
+    i32x4 v[3];
+  };
+  auto read_planes = [&](const unsigned char* base, int m, int ct, WPlanes& f) {
+    const int r = 32 * m + 4 * g + (l16 >> 2);
     const int sw = swz_row(4 * g + (l16 >> 2));
 #pragma unroll
-    for (int ct = 0; ct < NCT; ++ct) {
-      const unsigned char* p0 = base + (st % 3) * WPL + r * WROW +
-                                (((wc * NCT + ct) ^ sw) << 5) + 8 * (l16 & 3);
+    for (int pl = 0; pl < 3; ++pl) {
+      const unsigned char* p0 =
+          base + pl * WPL + r * WROW + (((wc * NCT + ct) ^ sw) << 5) + 8 * (l16 & 3);
       const walk_bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
           (SHC_WALK_LDS walk_bf16x4*)(const_cast<unsigned char*>(p0)));
       const walk_bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
           (SHC_WALK_LDS walk_bf16x4*)(const_cast<unsigned char*>(p0 + 16 * WROW)));
       const bf16x8 w = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-      f.v[ct] = __builtin_bit_cast(i32x4, w);
+      f.v[pl] = __builtin_bit_cast(i32x4, w);
     }
   };
   bool wild = false;  // split: an input value outside its range was met
@@ -487,8 +502,9 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
     }
     const bool live = (all & bits) != 0u;
     WFrag wf[2];
+    WPlanes wp[2];
     if (live) {
-      if constexpr (SPLIT) read_plane(base, 0, wf[0]);
+      if constexpr (SPLIT) read_planes(base, 0, 0, wp[0]);
       else read_w(base, 0, wf[0]);
     }
     issue_a(off, ahead);
@@ -505,14 +521,12 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
         for (int i = 0; i < 4; ++i) seen.see(cur[ks][i]);
       wild = wild || seen.outside(kSplitMaxA);
       // two k-steps of 32 entries; lane group g holds entries 4g .. 4g+3 of
-      // each of their two 16-entry halves.  Stage (m, plane): the plane's
-      // weights by every input term that with it makes a product above 2^-24
-      // of the whole (h by l, m, h; m by m, h; l by h)
+      // each of their two 16-entry halves
       bf16x8 at[3];
 #pragma unroll
-      for (int st = 0; st < 6; ++st) {
-        const int m = st / 3, pl = st % 3;
-        if (pl == 0) {
+      for (int st = 0; st < 2 * NCT; ++st) {
+        const int m = st / NCT, ct = st % NCT;
+        if (ct == 0) {
           walk_v4u32 t[3];
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
@@ -527,14 +541,19 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
 #pragma unroll
           for (int q = 0; q < 3; ++q) at[q] = __builtin_bit_cast(bf16x8, t[q]);
         }
-        if (st + 1 < 6) read_plane(base, st + 1, wf[(st + 1) & 1]);
+        if (st + 1 < 2 * NCT)
+          read_planes(base, (st + 1) / NCT, (st + 1) % NCT, wp[(st + 1) & 1]);
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 2 - pl; q >= 0; --q)
-#pragma unroll
-          for (int ct = 0; ct < NCT; ++ct)
-            acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                __builtin_bit_cast(bf16x8, wf[st & 1].v[ct]), at[q], acc[ct], 0, 0, 0);
+        auto mul = [&](int pl, int q, f32x4& sum) {
+          sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              __builtin_bit_cast(bf16x8, wp[st & 1].v[pl]), at[q], sum, 0, 0, 0);
+        };
+        mul(2, 0, low[ct]);
+        mul(0, 2, low[ct]);
+        mul(1, 1, low[ct]);
+        mul(1, 0, low[ct]);
+        mul(0, 1, low[ct]);
+        mul(0, 0, acc[ct]);
         __builtin_amdgcn_sched_barrier(0);
       }
       return;
@@ -570,18 +589,36 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
       phase(p0 + q, areg[q % NA], areg[(q + NA - 1) % NA], wreg[(q + 1) % NWS]);
   }
 
+  // The last MFMAs may sit right behind a branch; their results are read at
+  // least 32 wait states later (an fp32 16x16x4 needs 18).
+  auto mfma_wait = [] {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
   if constexpr (SPLIT) {
     // a lane's accumulators are row l16's, whose entries its four lane groups hold
     int out_of_range = (wild ? 1 : 0) | *w_wild;
     out_of_range |= __shfl_xor(out_of_range, 16, 64);
     out_of_range |= __shfl_xor(out_of_range, 32, 64);
     const bool redo = out_of_range != 0;
+    // the two sums and the bias, rounded once
+    mfma_wait();
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct) {
+      const f32x4 b = bias_of(ct);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        acc[ct][i] = (float)((double)acc[ct][i] + (double)low[ct][i] + (double)b[i]);
+    }
     if (__ballot(redo) != 0) {
       // the wavefront's rows again on the fp32 matrix cores, straight from memory
       f32x4 kept[NCT];
 #pragma unroll
-      for (int ct = 0; ct < NCT; ++ct) kept[ct] = acc[ct];
-      init_acc();
+      for (int ct = 0; ct < NCT; ++ct) {
+        kept[ct] = acc[ct];
+        acc[ct] = bias_of(ct);
+      }
 #pragma unroll 1
       for (int s = 0; s < nks; ++s) {
         const int lo = slot_of(s * KSTEP), hi = slot_of(min((s + 1) * KSTEP, Ktot) - 1);
@@ -608,10 +645,7 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
           }
         }
       }
-      // the last MFMAs may sit right behind the loop's branch (see below)
-      __builtin_amdgcn_sched_barrier(0);
-      asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
+      mfma_wait();
 #pragma unroll
       for (int ct = 0; ct < NCT; ++ct)
 #pragma unroll
@@ -620,11 +654,7 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
   }
 
   // ---- epilogue: activation, rounding, four columns of a row per store ---------
-  // The last MFMAs may sit right behind a branch; their results are read at
-  // least 32 wait states later (an fp32 16x16x4 needs 18).
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
+  mfma_wait();
   const bool relu = a.relu != 0;
   const __amdgpu_buffer_rsrc_t o_rsrc = __builtin_amdgcn_make_buffer_rsrc(
       a.out, (short)0, (int)(n * Cout * E), kWalkBufferWord3);

@@ -195,8 +195,8 @@ hipError_t launch_ws_gemm(const GemmArgs& a, bool conv, bool bf16, const WsPlan&
 bool conv_walk_supported(const GemmArgs& a, bool bf16);
 bool conv_walk_small(const GemmArgs& a, int num_cus);
 bool conv_walk_medium(const GemmArgs& a, int num_cus, int per_cu);
-// split: fp32 products of large shapes as exact sums of bf16 ones (not the
-// other kernels' bits)
+// split: fp32 products of large shapes from six bf16 ones (not the other
+// kernels' bits; the error against 64 bits is below theirs)
 hipError_t launch_conv_walk(const GemmArgs& a, bool bf16, bool split, int num_cus,
                             hipStream_t stream);
 // slot-major conv from a neighbour-row table (conv_sm.hip): bf16, C_in and

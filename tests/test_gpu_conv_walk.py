@@ -230,3 +230,24 @@ def test_conv_walk_split_mixed_magnitudes(dev, what):
     # value kept to 16 bits errs by 2^-17 = 7.6e-6)
     assert bool((err <= 1e-6 * scale + 2 * K * Cin * 2.0 ** -149).all()), \
         float((err / scale.clamp(min=1e-300)).max())
+
+
+@pytest.mark.parametrize("n,K,Cin,Cout", [(17001, 9, 128, 128), (33500, 9, 128, 128),
+                                          (40001, 3, 144, 80), (23000, 20, 48, 80)])
+@pytest.mark.parametrize("keep", [1.0, 0.5, 0.1, 0.03, 0.004])
+@pytest.mark.parametrize("with_bias", [False, True])
+def test_conv_walk_split_error(dev, n, K, Cin, Cout, keep, with_bias):
+    """The split's 2-norm error against 64 bits is no larger than the fp32
+    matrix cores' on the same values, from dense features to a few nonzero ones
+    a row.  Weights times 2^40 are outside the split's range and take the fp32
+    path: the same sums, scaled exactly."""
+    S, W, table, conv = split_problem(dev, n, K, Cin, Cout, n + K, keep)
+    bias = torch.randn(Cout, device=dev, generator=torch.Generator(dev).manual_seed(1)) \
+        if with_bias else None
+    ref, _ = dense_products(S, W, table, bias)
+    big = None if bias is None else bias * 2.0 ** 40
+    split = (conv(S, W, bias).double() - ref).norm() / ref.norm()
+    chain = (conv(S, W * 2.0 ** 40, big).double() * 2.0 ** -40 - ref).norm() / ref.norm()
+    print(f"n={n} K={K} {Cin}->{Cout} keep={keep} bias={with_bias}: split {split:.3e} fp32 {chain:.3e}")
+    # equal roundings where a row has few products: 1% for their chance
+    assert split <= 1.01 * chain, (float(split), float(chain))
