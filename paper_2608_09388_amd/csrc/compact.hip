@@ -20,7 +20,8 @@
 // the table entries of its rows -- whose neighbours lie in the same body --
 // come from LDS rather than from a second pass over `inv`.
 //
-// A mask of at most kOneLaunchBytes skips the count launch: every block counts
+// A mask of at most kOneLaunchBytes (and, with the table, of at most
+// kOneLaunchBodies) skips the count launch: every block counts
 // the bytes before its span itself (block 0 all of them).  At these sizes the
 // chain of launches is the cost, not the bytes: the count launch and the gap
 // behind it stood between the call and N' reaching the host.
@@ -531,6 +532,11 @@ void compact_plan(int64_t total, int32_t* nblocks, int64_t* per_block) {
 // Largest mask (in bytes read) whose blocks count for themselves: 16 loads a
 // thread of a 256-thread block, two rounds of memory latency.
 constexpr int64_t kOneLaunchBytes = 64 * 1024;
+// The table variant has a block per body, and each of them counts the whole
+// mask: past about a block per CU the counting is the cost (64 KB of mask,
+// two launches / one: 200 bodies 9.2 / 9.0 us, 400 9.4 / 11.2, 1,600 12.6 /
+// 22.6, 16,384 52 / 143).
+constexpr int32_t kOneLaunchBodies = 256;
 
 template <typename M>
 static hipError_t launch_compact_of(const M* mask, int32_t B, int32_t V, int32_t* coords,
@@ -605,7 +611,7 @@ hipError_t launch_compact_table(const uint8_t* mask, int32_t B, int32_t V, int32
   int32_t nblocks;
   int64_t per_block;
   compact_plan(total, &nblocks, &per_block);
-  if (total > kOneLaunchBytes) {
+  if (total > kOneLaunchBytes || B > kOneLaunchBodies) {
     hipLaunchKernelGGL(compact_count_kernel<uint8_t>, dim3(nblocks), dim3(kThreads), 0, stream,
                        mask, total, per_block, block_counts);
     const hipError_t err = hipGetLastError();

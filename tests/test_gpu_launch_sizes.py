@@ -36,11 +36,13 @@ def table_of(m, nbr):
 
 
 # the one-launch limit is 64 KB of mask: totals at and one past it, totals
-# that leave 1 to 15 bytes past a 16-byte group, bodies that start at any byte
+# that leave 1 to 15 bytes past a 16-byte group, bodies that start at any byte;
+# with the table, at and past 256 bodies
 @pytest.mark.parametrize("B,V,p", [(1, 1, 1.0), (3, 5, 0.5), (4, 655, 0.1), (1, 65535, 0.3),
                                    (1, 65536, 0.3), (1, 65537, 0.3), (16, 4096, 1.0),
                                    (5, 13107, 0.05), (13, 5041, 0.0), (13, 5042, 0.2),
-                                   (100, 655, 0.4), (101, 655, 0.4)])
+                                   (100, 655, 0.4), (101, 655, 0.4), (256, 255, 0.2),
+                                   (257, 37, 0.5), (16384, 4, 0.3)])
 def test_compaction_launches(dev, B, V, p):
     rng = np.random.default_rng(B * 977 + V)
     m = (rng.random((B, V)) < p).astype(np.uint8)
