@@ -26,7 +26,9 @@
 // v_permlane16_swap / v_permlane32_swap (VALU, no LDS traffic).
 // A body of up to kResident vectors per thread stays in registers, so HBM
 // sees one read and one write of every value; a larger body is streamed
-// three times (sums, deviations, output), the later passes mostly from L2.
+// three times (sums, deviations, output), the later passes mostly from L2,
+// kResident vectors per thread at a time (300 bodies of up to 10,475 rows x
+// 128 fp32, a tenth full: 338 us with one in flight, 221 us).
 #include <algorithm>
 #include <cmath>
 #include <mutex>
@@ -222,6 +224,17 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
 
   i32x4 keep[kResident];
   double acc[N];
+  // streamed bodies: kResident rows of a thread (r, r + TY, ...; zeros past the
+  // body) are in flight at once, so that a body the workgroup is small for
+  // costs its bytes rather than a memory latency a row
+  auto load_batch = [&](int r) {
+#pragma unroll
+    for (int k = 0; k < kResident; ++k) {
+      const bool in = r + k * TY < rows;
+      const i32x4 v = S[(lo + (in ? r + k * TY : 0)) * vpr + tx];
+      keep[k] = in ? v : i32x4{0, 0, 0, 0};
+    }
+  };
   // ---- pass 1: sums ------------------------------------------------------------
 #pragma unroll
   for (int e = 0; e < N; ++e) acc[e] = 0.0;
@@ -242,11 +255,15 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
       }
     }
   } else {
-    for (int r = ty; r < rows; r += TY) {
-      float f[N];
-      NV::widen(S[(lo + r) * vpr + tx], f);
+    for (int r = ty; r < rows; r += kResident * TY) {
+      load_batch(r);
 #pragma unroll
-      for (int e = 0; e < N; ++e) acc[e] += (double)f[e];
+      for (int k = 0; k < kResident; ++k) {
+        float f[N];
+        NV::widen(keep[k], f);
+#pragma unroll
+        for (int e = 0; e < N; ++e) acc[e] += (double)f[e];
+      }
     }
   }
   reduce(acc, false);
@@ -263,9 +280,9 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
   }
 
   // ---- pass 2: squared deviations from the group mean --------------------------
-  // A thread's squares (positive terms) are summed in fp32 over at most
-  // kResident rows at a time (relative error at most 15 * 2^-24), then the
-  // sums go on in fp64.
+  // A thread's squares (positive terms) are summed in fp32 over four rows at a
+  // time when resident (relative error at most 3 * 2^-24), kResident rows
+  // when streamed (15 * 2^-24); the sums go on in fp64.
 #pragma unroll
   for (int e = 0; e < N; ++e) acc[e] = 0.0;
   if (resident) {
@@ -297,12 +314,14 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
       float sq[N];
 #pragma unroll
       for (int e = 0; e < N; ++e) sq[e] = 0.f;
-      for (int r = r0; r < rows && r < r0 + kResident * TY; r += TY) {
+      load_batch(r0);
+#pragma unroll
+      for (int k = 0; k < kResident; ++k) {
         float f[N];
-        NV::widen(S[(lo + r) * vpr + tx], f);
+        NV::widen(keep[k], f);
 #pragma unroll
         for (int e = 0; e < N; ++e) {
-          const float d = (f[e] - mu_hi[e]) - mu_lo[e];
+          const float d = r0 + k * TY < rows ? (f[e] - mu_hi[e]) - mu_lo[e] : 0.f;
           sq[e] = __builtin_fmaf(d, d, sq[e]);
         }
       }
@@ -331,7 +350,12 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
     for (int k = 0; k < kResident; ++k)
       if (k * TY < rows && ty + k * TY < rows) emit(keep[k], ty + k * TY);
   } else {
-    for (int r = ty; r < rows; r += TY) emit(S[(lo + r) * vpr + tx], r);
+    for (int r = ty; r < rows; r += kResident * TY) {
+      load_batch(r);
+#pragma unroll
+      for (int k = 0; k < kResident; ++k)
+        if (r + k * TY < rows) emit(keep[k], r + k * TY);
+    }
   }
 }
 
@@ -357,7 +381,13 @@ int group_norm_split(int32_t B, int32_t C, int32_t G, int is_bf16, int num_cus) 
 // and a thread per channel in the reductions.  Several workgroups then share
 // a CU, so one's barriers and memory latency hide behind the others, and
 // short bodies leave no threads without rows.  2,048 frames of 65 rows x 256
-// fp32: 71.4 us with 1024 threads, 44.9 us with 512 (6.1 TB/s of 274 MB).
+// fp32: 71.4 us with 1024 threads, 44.9 us with 512 (6.1 TB/s of 274 MB).  A
+// body far above the mean is streamed by few threads: 300 bodies of 655 x 128
+// fp32, a tenth of them full and the others empty, 17.4 us with 1024 threads,
+// 24.6 with 256 (42 with one row of a thread in flight); the same body alone
+// among bodies of 65 rows 17.5 and 24.5 (40.5); 2,048 frames of geometric
+// sizes x 256 bf16 103 and 49 (67).  Even 300 bodies take 15.2 and 8.8, and
+// which of the two a mask is the host does not know.
 static int group_norm_threads(int64_t n_rows, int32_t B, int32_t C, int is_bf16, int split,
                               int num_cus) {
   if ((int64_t)B * split <= num_cus) return kNormThreads;

@@ -113,6 +113,27 @@ def test_short_bodies_norm_and_pool(dev, dtype, B, V, C, G, p):
     assert np.array_equal(down(P), O.segment_max(S.astype(np.float64), rp, -2.0))
 
 
+# a few bodies longer than the workgroup's registers hold (64 rows of 256 fp32
+# channels, 128 of bf16, 256-thread workgroups), streamed in batches of that
+# many rows: at and beside whole batches, and many of them
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_norm_streams_long_bodies(dev, dtype):
+    B, C, G = 600, 256, 32
+    rng = np.random.default_rng(9)
+    rows = rng.integers(0, 12, size=B)
+    rows[:12] = [63, 64, 65, 127, 128, 129, 191, 192, 193, 256, 257, 2500]
+    rp = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    n = int(rp[-1])
+    S = (rng.standard_normal((n, C)) * 2.0 + rng.standard_normal(C) * 3.0).astype(np.float32)
+    S = synth.as_dtype(S, dtype)[1]
+    out = torch.full((n + 3, C), float("nan"), dtype=TORCH[dtype], device=dev)
+    shc.segment_group_norm(up(S, dtype), up(rp), n, B, G, out)
+    got = down(out)
+    assert np.all(np.isnan(got[n:]))
+    assert_gn_close(got[:n], O.group_norm(S.astype(np.float64), rp, G), dtype,
+                    gn_floor(S, rp, G), "group norm of long bodies")
+
+
 @pytest.mark.parametrize("V,n,K", [(40, 1, 1), (200, 63, 9), (200, 64, 9), (300, 65, 5),
                                    (655, 1300, 9)])
 def test_transposed_table_blocks(dev, V, n, K):
