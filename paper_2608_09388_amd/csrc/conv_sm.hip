@@ -3,29 +3,29 @@
 //
 //   out[i] = act( bias + sum_{j<K} S[table[j][i]] W[j] ),  absent entries add 0.
 //
-// A workgroup owns 128 or 320 consecutive active rows and every output
+// A workgroup owns 128, 192 or 320 consecutive active rows and every output
 // column.  It walks the slots in order: the weights of slot j (Cin x Cout)
 // sit in LDS while every wavefront multiplies its rows' slot-j neighbour rows
 // by them, and slot j + 1's weights are loaded beside that work into the
 // other of two buffers; the neighbour rows of slot j + 1 are in flight in
-// registers meanwhile.  Each gathered row therefore feeds all Cout
-// columns at once.  Rows are sorted by their first sparse slot, and a (16-row
-// block, slot) pair with no present row is skipped.  Accumulation is in fp32, per output element
-// in slot order and within a slot in k order.
+// registers meanwhile.  Each gathered row therefore feeds all Cout columns at
+// once.  Rows are sorted by their first sparse slot, and a (16-row block,
+// slot) pair with no present row is skipped.  Accumulation is in fp32, per
+// output element in slot order and within a slot in k order.
 //
 // What bounds it: a slot's weight reads from LDS and its MFMAs take about as
 // long each, and the table reads, the sort and the output around the slots
 // would stand beside neither.  So a workgroup takes half a CU's LDS or less
-// (128 rows, the output staged where the weights were) and two or more share
-// a CU, one's slots under another's ends; with one of 256 rows a CU those ends
-// were 59 of 273 us (670,464 rows at half density, 128 -> 128 channels, nine
-// slots; 257 us with two).  At 600,000 rows, half dense: 64 -> 128 149 ->
-// 130 us, 128 -> 64 170 -> 136; seven slots 128 -> 128 278 -> 215.  Sparse
-// masks at 128 -> 128 and nine slots are even (10%, 600,000 rows: 213, 212) or
-// pay a little for weights loaded per 128 rows (5%, 258,000: 81, 86).  Each
-// XCD takes a contiguous run of rows: 281 against 275 us.  A read of
-// the weights half a k-step ahead of the MFMAs, or two slots of rows in
-// flight instead of one, is slower (262 and 264 against 257 us).
+// (the output staged where the weights were) and two or more share a CU, one's
+// slots under another's ends; with one of 256 rows a CU those ends were 59 of
+// 273 us (670,464 rows at half density, 128 -> 128 channels, nine slots; 257
+// us with two of 128 rows, 220 with two of 192).  At 600,000 rows, half dense:
+// 64 -> 128 149 -> 130 us, 128 -> 64 170 -> 136; seven slots 128 -> 128 278 ->
+// 179.  On sparse masks the weights of every slot, loaded per workgroup, are
+// the larger part (launch_sm_rows).  Each XCD takes a contiguous run of rows:
+// 281 against 275 us.  A read of the weights half a k-step ahead of the MFMAs,
+// or two slots of rows in flight instead of one, is slower (262 and 264
+// against 257 us, 128 rows).
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -65,9 +65,9 @@ __host__ __device__ constexpr int sm_work_bytes(int cin, int cout, int nw) {
 __host__ __device__ inline int sm_lds_bytes(int cin, int cout, int K, int R, int nw) {
   return sm_work_bytes(cin, cout, nw) + ((sm_idx_bytes(K, R) + 15) & ~15);
 }
-// Two workgroups of 128 rows (whichever wavefronts) to a CU
-inline bool sm_two_per_cu(int cin, int cout, int K) {
-  return sm_lds_bytes(cin, cout, K, 128, 8) <= kSmLdsLimit / 2;
+// Two workgroups of R rows (whichever wavefronts) to a CU
+inline bool sm_two_per_cu(int cin, int cout, int K, int R) {
+  return sm_lds_bytes(cin, cout, K, R, R / 16) <= kSmLdsLimit / 2;
 }
 
 struct SmArgs {
@@ -86,8 +86,10 @@ struct SmArgs {
 // rows per workgroup); KF: K fixed at compile time (the slots fully
 // unrolled), or 0 for any K (a loop over the slots, whose back edge makes the
 // compiler wait for every load in flight); MINW: wavefronts per SIMD the
-// registers leave room for.
-template <int KS, int NCT, int NW, int BPW, int KF, int MINW>
+// registers leave room for; ASETS: register sets of neighbour rows (two: slot
+// j + 1's go out ahead of slot j's MFMAs; one: each k-step's registers take
+// slot j + 1's as soon as slot j's MFMAs have read them).
+template <int KS, int NCT, int NW, int BPW, int KF, int MINW, int ASETS>
 __global__ __launch_bounds__(64 * NW, MINW) void conv_sm_kernel(const SmArgs a) {
   constexpr int NT = 64 * NW;
   constexpr int Cin = KS * 32;
@@ -256,20 +258,26 @@ __global__ __launch_bounds__(64 * NW, MINW) void conv_sm_kernel(const SmArgs a) 
   // loads, an absent row reading zeros without touching memory
   const __amdgpu_buffer_rsrc_t s_rsrc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<void*>(a.S), (short)0, (int)(n * Cin * 2), kSmBufferWord3);
-  i32x4 areg[2][BPW][KS];
-  auto issue_a = [&](int j, i32x4 (&dst)[BPW][KS]) {
+  i32x4 areg[ASETS][BPW][KS];
+  auto offsets = [&](int j, uint32_t (&off)[BPW]) {
 #pragma unroll
     for (int u = 0; u < BPW; ++u) {
-      const int row = (wave * BPW + u) * 16 + l16;
-      const int32_t src = j < K ? srcs[j * R + row] : -1;
-      const uint32_t off = src >= 0 ? (uint32_t)src * (uint32_t)(Cin * 2) + (uint32_t)g * 16u
-                                    : kSmOutOfRange;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        dst[u][ks] = __builtin_bit_cast(
-            i32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                       s_rsrc, src >= 0 ? off + (uint32_t)ks * 64u : kSmOutOfRange, 0, 0));
+      const int32_t src = j < K ? srcs[j * R + (wave * BPW + u) * 16 + l16] : -1;
+      off[u] = src >= 0 ? (uint32_t)src * (uint32_t)(Cin * 2) + (uint32_t)g * 16u : kSmOutOfRange;
     }
+  };
+  auto load_a = [&](uint32_t off, int ks) -> i32x4 {
+    return __builtin_bit_cast(
+        i32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                   s_rsrc, off != kSmOutOfRange ? off + (uint32_t)ks * 64u : kSmOutOfRange, 0, 0));
+  };
+  auto issue_a = [&](int j, i32x4 (&dst)[BPW][KS]) {
+    uint32_t off[BPW];
+    offsets(j, off);
+#pragma unroll
+    for (int u = 0; u < BPW; ++u)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) dst[u][ks] = load_a(off[u], ks);
   };
 
   // accumulators start at the bias of their column
@@ -286,7 +294,7 @@ __global__ __launch_bounds__(64 * NW, MINW) void conv_sm_kernel(const SmArgs a) 
   issue_a(0, areg[0]);
   load_w(K > 1 ? 1 : K - 1);
 
-  // ---- the slots, in order; register set and weight buffer j % 2
+  // ---- the slots, in order; register set j % ASETS, weight buffer j % 2
   auto slot = [&](int j, i32x4 (&cur)[BPW][KS], i32x4 (&ahead)[BPW][KS]) {
     // slot j's weights were stored before this barrier; every wavefront is
     // done with slot j - 1, so its buffer takes slot j + 1's, and their
@@ -296,7 +304,9 @@ __global__ __launch_bounds__(64 * NW, MINW) void conv_sm_kernel(const SmArgs a) 
     __syncthreads();
     store_w((j + 1) & 1);
     load_w(j + 2 < K ? j + 2 : K - 1);
-    issue_a(j + 1, ahead);
+    uint32_t off[BPW];
+    if constexpr (ASETS == 2) issue_a(j + 1, ahead);
+    else offsets(j + 1, off);
     bool live[BPW];
     bool any = false;
 #pragma unroll
@@ -304,28 +314,35 @@ __global__ __launch_bounds__(64 * NW, MINW) void conv_sm_kernel(const SmArgs a) 
       live[u] = pres[j * (R / 16) + wave * BPW + u] != 0;
       any = any || live[u];
     }
-    if (!any) return;  // no row of this wavefront has slot j: no B reads either
+    // a wavefront none of whose rows has slot j reads no weights either
+    if (ASETS == 2 && !any) return;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      bf16x8 bfr[NCT];
-      read_b(j & 1, ks, bfr);
+      if (any) {
+        bf16x8 bfr[NCT];
+        read_b(j & 1, ks, bfr);
 #pragma unroll
-      for (int u = 0; u < BPW; ++u) {
-        if (!live[u]) continue;
-        const bf16x8 af = __builtin_bit_cast(bf16x8, cur[u][ks]);
+        for (int u = 0; u < BPW; ++u) {
+          if (!live[u]) continue;
+          const bf16x8 af = __builtin_bit_cast(bf16x8, cur[u][ks]);
 #pragma unroll
-        for (int ct = 0; ct < NCT; ++ct)
-          acc[u][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfr[ct], acc[u][ct], 0, 0, 0);
+          for (int ct = 0; ct < NCT; ++ct)
+            acc[u][ct] =
+                __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfr[ct], acc[u][ct], 0, 0, 0);
+        }
       }
+      if constexpr (ASETS == 1)
+#pragma unroll
+        for (int u = 0; u < BPW; ++u) cur[u][ks] = load_a(off[u], ks);
     }
   };
   if constexpr (KF > 0) {
 #pragma unroll
-    for (int j = 0; j < KF; ++j) slot(j, areg[j & 1], areg[(j + 1) & 1]);
+    for (int j = 0; j < KF; ++j) slot(j, areg[j % ASETS], areg[(j + 1) % ASETS]);
   } else {
     for (int j0 = 0; j0 < K; j0 += 2) {
-      slot(j0, areg[0], areg[1]);
-      if (j0 + 1 < K) slot(j0 + 1, areg[1], areg[0]);
+      slot(j0, areg[0], areg[1 % ASETS]);
+      if (j0 + 1 < K) slot(j0 + 1, areg[1 % ASETS], areg[0]);
     }
   }
   __syncthreads();  // the staging tiles take the weights' place
@@ -385,10 +402,10 @@ __global__ __launch_bounds__(64 * NW, MINW) void conv_sm_kernel(const SmArgs a) 
   }
 }
 
-template <int KS, int NCT, int NW, int BPW, int KF, int MINW = 2>
+template <int KS, int NCT, int NW, int BPW, int KF, int MINW = 2, int ASETS = 2>
 hipError_t launch_sm(const SmArgs& a, hipStream_t stream) {
   constexpr int R = BPW * 16 * NW;
-  auto kern = conv_sm_kernel<KS, NCT, NW, BPW, KF, MINW>;
+  auto kern = conv_sm_kernel<KS, NCT, NW, BPW, KF, MINW, ASETS>;
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [&] {
@@ -402,28 +419,37 @@ hipError_t launch_sm(const SmArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <int KS, int NCT, int NW, int BPW>
+template <int KS, int NCT, int NW, int BPW, int ASETS = 2>
 hipError_t launch_sm_k(const SmArgs& a, hipStream_t stream) {
   // nine slots unrolled: 4 to 10% (236 against 247 us at 600,000 half-dense
   // rows, 128 -> 128)
-  return a.K == 9 ? launch_sm<KS, NCT, NW, BPW, 9>(a, stream)
-                  : launch_sm<KS, NCT, NW, BPW, 0>(a, stream);
+  return a.K == 9 ? launch_sm<KS, NCT, NW, BPW, 9, 2, ASETS>(a, stream)
+                  : launch_sm<KS, NCT, NW, BPW, 0, 2, ASETS>(a, stream);
 }
 
-// 128 rows per workgroup where two fit a CU's LDS: eight wavefronts of one
-// block for 64 input channels, four of two blocks (a weight fragment read
-// feeds both) for 128, whose registers hold two wavefronts per SIMD either
-// way (128 -> 128 at 100,000 rows: 43 to 54 against 55 to 65 us with eight;
-// 64 -> 128: 24 to 30 with eight against 27 to 31), and for 64 -> 64 past the
-// rows the chip holds at once (300,000 rows, seven slots: 37 against 40 us,
-// at 80,000 13 against 14 the other way).  Else (128 -> 128 with 15 slots or
-// more) 320 rows: one wavefront per SIMD holding five blocks.
+// Two workgroups to a CU's LDS, of 128 rows: eight wavefronts of one block for
+// 64 input channels, four of two blocks (a weight fragment read feeds both)
+// for 128 -> 64 (64 -> 128: 24 to 30 us with eight at 100,000 rows against 27
+// to 31), and for 64 -> 64 past the rows the chip holds at once (300,000 rows,
+// seven slots: 37 against 40 us, at 80,000 13 against 14 the other way).
+// 128 -> 128 takes 192 rows, four wavefronts of three blocks with one register
+// set of rows, up to ten slots, where two fit, and from 500 rows per CU (nine
+// slots, 131,000 rows at 5% 45.9 against 43.5 us; ten slots 51.3 against 50.7,
+// 100,000 rows 47.2 against 51.2): a third fewer weight bytes from
+// L2 (each workgroup reads all of them, 32 KB a slot), which bound its sparse
+// masks (nine slots, 258,048 rows at 5% 84.2 us with 128 rows, 75.1 with 192,
+// 80.5 with one workgroup of 256 a CU; 600,000 at 50% 232, 197 and 255).  Eleven to fourteen slots 128 rows (192 leave one workgroup a
+// CU: 100,000 rows, eleven slots, 50 against 76 us), 15 and more 320 rows: one
+// wavefront per SIMD holding five blocks.
 template <int KS, int NCT>
 hipError_t launch_sm_rows(const SmArgs& a, int num_cus, hipStream_t stream) {
   if constexpr (KS == 4) {
-    if constexpr (NCT == 8)
-      if (!sm_two_per_cu(KS * 32, NCT * 16, a.K))
+    if constexpr (NCT == 8) {
+      if (sm_two_per_cu(KS * 32, NCT * 16, a.K, 192) && a.n_rows >= 500LL * num_cus)
+        return launch_sm_k<KS, NCT, 4, 3, 1>(a, stream);
+      if (!sm_two_per_cu(KS * 32, NCT * 16, a.K, 128))
         return launch_sm<KS, NCT, 4, 5, 0, 1>(a, stream);
+    }
     return launch_sm_k<KS, NCT, 4, 2>(a, stream);
   } else {
     if constexpr (NCT == 4)
@@ -441,11 +467,11 @@ bool conv_sm_supported(const GemmArgs& a, bool bf16) {
   if (!((a.Cin == 64 || a.Cin == 128) && (a.Cout == 64 || a.Cout == 128))) return false;
   // 32-bit buffer offsets
   if (a.n_rows * a.Cin * 2 > 0x7FFF0000LL || a.n_rows * a.Cout * 2 > 0x7FFF0000LL) return false;
-  return sm_two_per_cu(a.Cin, a.Cout, a.K) ||
+  return sm_two_per_cu(a.Cin, a.Cout, a.K, 128) ||
          sm_lds_bytes(a.Cin, a.Cout, a.K, 320, 4) <= kSmLdsLimit;
 }
 
-bool conv_sm_two(const GemmArgs& a) { return sm_two_per_cu(a.Cin, a.Cout, a.K); }
+bool conv_sm_two(const GemmArgs& a) { return sm_two_per_cu(a.Cin, a.Cout, a.K, 128); }
 
 hipError_t launch_conv_sm(const GemmArgs& g, int num_cus, hipStream_t stream) {
   SmArgs a;

@@ -73,8 +73,8 @@ def test_conv_sm_shapes_against_oracle(dev, B, V, K, Cin, Cout, p, mesh):
     torch.cuda.synchronize()
 
 
-# 128-row workgroups, two to a CU, their output staged where the weights were:
-# eight wavefronts and four, a last group that is nearly empty, one and two
+# 128- and 192-row workgroups, two to a CU, their output staged where the weights
+# were: eight wavefronts and four, a last group that is nearly empty, one and two
 # slots (the staging tiles then reach past the weights), an odd and an even
 # slot count of the loop, and the 320-row form where two do not fit; then either
 # side of the lines to the tiled kernel (few slots, short and wide reductions,
@@ -83,6 +83,7 @@ def test_conv_sm_shapes_against_oracle(dev, B, V, K, Cin, Cout, p, mesh):
     (129, 1, 64, 128), (2 * 128 + 1, 2, 64, 64), (65536, 5, 64, 64), (65537, 9, 64, 64),
     (65537, 6, 64, 64), (40001, 12, 128, 64), (32769, 11, 128, 128), (32900, 14, 128, 128),
     (256000, 9, 128, 64), (256003, 15, 128, 128),
+    (192 * 1334 + 1, 9, 128, 128), (256000 + 191, 1, 128, 128), (33001, 10, 128, 128),
     (32768, 5, 48, 80), (32769, 5, 48, 80), (16384, 5, 16, 256), (16385, 5, 16, 256),
     (32769, 12, 96, 256),
 ])
