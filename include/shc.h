@@ -789,9 +789,11 @@ int shc_event_destroy(void* event);
  * three (the host waits for a set's previous scatter and pool to finish
  * before compacting into it).  At the end of a run the run's stream waits
  * for the other two, so work enqueued on it afterwards sees every output.
- * A run for which the three streams do not pay (fewer than 8 batches, a feed,
- * no dense output, or under 300,000 entries B*V) takes the serial schedule on
- * the run's stream; its results are the same, bit for bit.
+ * A run for which the three streams do not pay takes the serial schedule on
+ * the run's stream: one of fewer than 8 batches or without a dense output;
+ * without a feed, under 300,000 entries B*V; with a feed, an incremental
+ * scatter or a dense output under 200 MB.  Its results are the same, bit for
+ * bit.
  */
 #define SHC_STACK_MAX_LAYERS 16
 #define SHC_LAYER_LINEAR 0 /* Eq. 6 */
@@ -866,7 +868,9 @@ typedef struct shc_stack_desc {
 /* Batch-input callback of shc_stack_run: called just before the compaction
  * of batch `batch` (0-based within the run) is enqueued; it may write that
  * batch's mask and x with work on `stream` (the stream that batch's
- * compaction runs on, ordered after the gather of batch - 1).  A nonzero return ends the run with SHC_ERR_INVALID_ARG. */
+ * compaction runs on, ordered after the gather of batch - 1: the side stream
+ * in a pipelined run, but for batch 0, and the run's stream otherwise).  A
+ * nonzero return ends the run with SHC_ERR_INVALID_ARG. */
 typedef int (*shc_stack_feed_fn)(void* user, int64_t batch, hipStream_t stream);
 
 /*

@@ -64,7 +64,7 @@ struct Stack {
   // that layer builds, -1 without a plan
   int plan_owner[SHC_STACK_MAX_LAYERS];
   // stream-ordering events (device scope; see shc_event_create)
-  hipEvent_t set_free[3] = {}, ready = nullptr;
+  hipEvent_t set_free[3] = {}, ready = nullptr, x_read = nullptr;
   hipEvent_t last_done[2] = {}, tail_done[2] = {}, tail_end = nullptr;
   bool busy = false;
 
@@ -202,7 +202,7 @@ struct Stack {
 
   // every layer of batch k on set s (the last one into `last`)
   int layers(const RunArgs& a, int64_t k, int s, int64_t n, void* last, hipStream_t st,
-             hipEvent_t before_last) const {
+             hipEvent_t before_last, hipEvent_t after_first) const {
     for (int l = 0; l < d.n_layers; ++l) {
       void* dst = d.acts[l + 1];
       if (l == d.n_layers - 1) {
@@ -213,6 +213,8 @@ struct Stack {
       STK_TRY(record_time(a, k, 0, l));
       STK_TRY(layer(s, l, n, dst, st));
       STK_TRY(record_time(a, k, 1, l));
+      if (l == 0 && fused_gather && after_first != nullptr)
+        STK_TRY(hip_err(hipEventRecord(after_first, st), "stack: record"));
     }
     return SHC_OK;
   }
@@ -229,7 +231,7 @@ struct Stack {
       STK_TRY(table(s, n, st));
       STK_TRY(plans(s, n, st));
       STK_TRY(gather(s, n, st));
-      STK_TRY(layers(a, k, s, n, d.acts[d.n_layers], st, nullptr));
+      STK_TRY(layers(a, k, s, n, d.acts[d.n_layers], st, nullptr, nullptr));
       int nxt = -1;
       if (k + 1 < a.steps) {
         nxt = (s + 1) % d.n_sets;
@@ -250,34 +252,54 @@ struct Stack {
   // Whether a run of a stack with side and tail streams uses them.  The three
   // streams hide the dispatch gaps between a batch's layers and the scatter
   // before it, and cost cross-stream waits, a fill and a drain.  Measured, us a
-  // batch, one stream / three (bf16, 5 to 10% masks):
-  //   no feed, 1.34 M entries, linear + conv 128, scatter and pool:
-  //     2 batches 107 / 127, 4 107 / 104, 8 107 / 100, 256 107 / 96;
-  //   no feed, 335 K entries: 4 batches 58 / 62, 8 58 / 56, 256 57 / 54;
-  //   no feed, 62 K entries: 8 batches 37 / 57, 256 36 / 39;
-  //   no dense output (three 256-channel convs): 4 batches 281 / 286, 256
-  //     281 / 279;
-  //   fed batches (the feed waits for the last gather across streams):
-  //     1.34 M entries 110 / 119 (4), 109 / 112 (256); 62 K entries 48 / 70
-  //     (4), 38 / 58 (256).
+  // batch, one stream / three, each stack in a process of its own (bf16 linear +
+  // conv, 5% masks, scatter and pool; "fed": a feed that copies a mask):
+  //   no feed, 1.34 M entries, C 128: 4 batches 114 / 120, 8 111 / 109, 300
+  //     107 / 95; 335 K entries: 8 61 / 66, 300 57 / 58; 62 K entries: 256
+  //     36 / 39;
+  //   no feed, no dense output (three 256-channel convs): 4 batches 281 / 286,
+  //     256 281 / 279;
+  //   fed (the feed waits for the last gather across streams), by the bytes of
+  //     the dense output, whose scatter is what the second stream hides:
+  //     343 MB (1.34 M entries x 128) 4 batches 118 / 122, 8 113 / 106, 300
+  //     109 / 93 (with a feed that writes x as well 284 / 249); 257 MB 8
+  //     97 / 93, 300 93 / 83; 172 MB 300 76 / 71 (670 K x 128), 92 / 86 (670 K
+  //     of 655 vertices) and 75 / 81 (1.34 M x 64); 86 MB 300 60 / 77;
+  //   fed, incremental scatter (little to hide): 343 MB 300 73 / 79.
   // A serial run leaves nothing on the other streams, and the next run's first
   // count arrives behind all of its work, so runs may alternate.
   bool pipeline_pays(const RunArgs& a) const {
-    return a.feed == nullptr && a.steps >= 8 && d.dense_out != nullptr && cap() >= 300000;
+    if (a.steps < 8 || d.dense_out == nullptr) return false;
+    if (a.feed == nullptr) return cap() >= 300000;
+    return !d.incremental && cap() * c_last * (d.dtype == SHC_BF16 ? 2 : 4) >= 200000000;
   }
 
   // three streams: batch k's layers on the run's stream, batch k + 1's
   // compaction (table, plans) on the side stream, batch k's scatter and pool
   // on the tail stream; the last layer's output alternates between two
-  // buffers and the index sets rotate over three.  Runs without a feed only
-  // (pipeline_pays)
+  // buffers and the index sets rotate over three
   int run_pipelined(const RunArgs& a, int* cur, int64_t* prev_rows, int64_t* n_last) const {
+    const int rc = pipelined_batches(a, cur, prev_rows, n_last);
+    // work enqueued on the run's stream afterwards sees every output; a run
+    // that ended early (a feed's error) leaves no work behind either
+    STK_TRY(hip_err(hipEventRecord(tail_end, d.tail), "stack: record"));
+    STK_TRY(hip_err(hipStreamWaitEvent(a.main, tail_end, 0), "stack: wait"));
+    if (rc != SHC_OK) {
+      STK_TRY(hip_err(hipEventRecord(ready, d.side), "stack: record"));
+      STK_TRY(hip_err(hipStreamWaitEvent(a.main, ready, 0), "stack: wait"));
+    }
+    return rc;
+  }
+
+  int pipelined_batches(const RunArgs& a, int* cur, int64_t* prev_rows, int64_t* n_last) const {
     hipStream_t main = a.main, side = d.side, tail = d.tail;
     bool set_used[3] = {false, false, false};
     bool buf_used[2] = {false, false};
     void* const last_buf[2] = {d.acts[d.n_layers], d.last_alt};
+    const bool feeding = a.feed != nullptr;
     int s = *cur;
     int64_t n = 0;
+    STK_TRY(feed_batch(a, 0, main));
     STK_TRY(compact_start(s, main));
     STK_TRY(compact_wait(s, main, &n));
     bool front_done = false;  // table and plans of set s already built (side stream)
@@ -288,13 +310,22 @@ struct Stack {
         STK_TRY(plans(s, n, main));
       }
       STK_TRY(gather(s, n, main));
-      STK_TRY(layers(a, k, s, n, last_buf[i], main, buf_used[i] ? tail_done[i] : nullptr));
+      if (!fused_gather && feeding)
+        STK_TRY(hip_err(hipEventRecord(x_read, main), "stack: record"));
+      STK_TRY(layers(a, k, s, n, last_buf[i], main, buf_used[i] ? tail_done[i] : nullptr,
+                     feeding ? x_read : nullptr));
       STK_TRY(hip_err(hipEventRecord(last_done[i], main), "stack: record"));
       buf_used[i] = true;
       // compaction of batch k + 1 (side stream)
       int nxt = -1;
       if (k + 1 < a.steps) {
         nxt = (s + 1) % 3;
+        if (feeding) {
+          // batch k + 1's inputs are written once batch k's gather has read x
+          // (batch k's compaction read the mask earlier on this stream)
+          STK_TRY(hip_err(hipStreamWaitEvent(side, x_read, 0), "stack: wait"));
+          STK_TRY(feed_batch(a, k + 1, side));
+        }
         // the set was last read by the scatter and pool of batch k - 2
         if (set_used[nxt])
           STK_TRY(hip_err(hipEventSynchronize(set_free[nxt]), "stack: set reuse wait"));
@@ -318,8 +349,6 @@ struct Stack {
         n = n_next;
       }
     }
-    STK_TRY(hip_err(hipEventRecord(tail_end, tail), "stack: record"));
-    STK_TRY(hip_err(hipStreamWaitEvent(main, tail_end, 0), "stack: wait"));
     *cur = s;
     *n_last = n;
     return SHC_OK;
@@ -549,7 +578,7 @@ int shc_stack_create(const shc_stack_desc* desc, void** stack) {
   if (rc == SHC_OK) rc = hip_err(hipGetDevice(&k->device), "stack: current device");
   const unsigned flags = hipEventDisableTiming | hipEventDisableSystemFence;
   for (hipEvent_t* e : {&k->set_free[0], &k->set_free[1], &k->set_free[2], &k->ready,
-                        &k->last_done[0], &k->last_done[1], &k->tail_done[0],
+                        &k->x_read, &k->last_done[0], &k->last_done[1], &k->tail_done[0],
                         &k->tail_done[1], &k->tail_end})
     if (rc == SHC_OK) rc = hip_err(hipEventCreateWithFlags(e, flags), "stack: event create");
   if (rc != SHC_OK) {

@@ -575,12 +575,13 @@ class SparseStack:
         ``feed(k)``, if given, is called just before batch k's compaction is
         enqueued and may write batch k's mask and features into ``mask`` and
         ``x`` with work on the stream current when it is called (the side
-        stream in a pipelined run from Python, after the gather of batch
-        k - 1, else the stack's own stream, on which the native loop runs fed
-        batches; without it every batch reuses them).  ``around_layer = (l, [(ev_a, ev_b), ...])`` records one pair of
-        events around layer l of every batch (a pair of None: none for that
-        batch).  The outputs left behind are the
-        last batch's.  Returns its N'."""
+        stream in a pipelined run, after the gather of batch k - 1, else the
+        stack's own; the native loop pipelines fed runs of 8 batches or more
+        whose zero-fill scatter writes 200 MB or more); without it every batch
+        reuses them.  ``around_layer = (l, [(ev_a, ev_b), ...])`` records one
+        pair of events around layer l of every batch (a pair of None: none for
+        that batch).  The outputs left behind are the last batch's.  Returns
+        its N'."""
         if steps <= 0:
             return self.n or 0
         cur = self._enter()
