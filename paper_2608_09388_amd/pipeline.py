@@ -551,8 +551,10 @@ class SparseStack:
         if self._native is not None and self.side is None:
             cur = self._enter()
             try:
-                n, self._cur, self.prev_n = self._native.run(
-                    1, self.main, cur_set=self._cur, prev_rows=self.prev_n)
+                # on the stack's stream and device, whatever is current
+                with torch.cuda.stream(self.main):
+                    n, self._cur, self.prev_n = self._native.run(
+                        1, self.main, cur_set=self._cur, prev_rows=self.prev_n)
             finally:
                 self._leave(cur)
             self._set.n = n
