@@ -44,6 +44,8 @@ library's kernels.
 """
 from __future__ import annotations
 
+import contextlib
+
 from typing import Callable, Dict, Optional, Sequence, Tuple
 
 import numpy as np
@@ -551,8 +553,10 @@ class SparseStack:
         if self._native is not None and self.side is None:
             cur = self._enter()
             try:
-                # on the stack's stream and device, whatever is current
-                with torch.cuda.stream(self.main):
+                # on the stack's device, whichever is current (a switch costs
+                # the host microseconds: only where there is one)
+                here = torch.cuda.current_device() == self.main.device_index
+                with contextlib.nullcontext() if here else torch.cuda.stream(self.main):
                     n, self._cur, self.prev_n = self._native.run(
                         1, self.main, cur_set=self._cur, prev_rows=self.prev_n)
             finally:
