@@ -798,6 +798,9 @@ int shc_event_destroy(void* event);
 #define SHC_STACK_MAX_LAYERS 16
 #define SHC_LAYER_LINEAR 0 /* Eq. 6 */
 #define SHC_LAYER_CONV 1   /* Eqs. 4-5 */
+#define SHC_STACK_AUTO 0      /* the schedule that the rule above gives */
+#define SHC_STACK_SERIAL 1    /* the run's stream alone */
+#define SHC_STACK_PIPELINED 2 /* three streams (a stack with side and tail only) */
 
 typedef struct shc_stack_layer {
   int32_t kind;      /* SHC_LAYER_LINEAR or SHC_LAYER_CONV */
@@ -889,6 +892,8 @@ typedef int (*shc_stack_feed_fn)(void* user, int64_t batch, hipStream_t stream);
  *   failing call's status; work enqueued before it stays enqueued (the caller
  *   synchronises the streams before reusing the buffers).  Only one run at a
  *   time per executor.
+ * shc_stack_set_schedule -- the schedule of the following runs, whatever they
+ *   gain by it (SHC_STACK_AUTO at creation); between runs only.
  * shc_stack_destroy -- releases the executor (NULL is ignored); runs that
  *   used it must have finished.
  */
@@ -896,6 +901,7 @@ int shc_stack_create(const shc_stack_desc* desc, void** stack);
 int shc_stack_run(void* stack, int64_t steps, hipStream_t stream, shc_stack_feed_fn feed,
                   void* user, int32_t time_layer, void* const* time_events, int32_t* cur_set,
                   int64_t* prev_rows, int64_t* n_last);
+int shc_stack_set_schedule(void* stack, int32_t schedule);
 int shc_stack_destroy(void* stack);
 
 #ifdef __cplusplus

@@ -44,6 +44,7 @@ _c_i32, _c_i64, _c_ptr, _c_sz, _c_f = (ctypes.c_int32, ctypes.c_int64, ctypes.c_
 # stack executor (shc_stack_*): mirrors of the C structs, same field order
 STACK_MAX_LAYERS = 16
 SHC_LAYER_LINEAR, SHC_LAYER_CONV = 0, 1
+SHC_STACK_AUTO, SHC_STACK_SERIAL, SHC_STACK_PIPELINED = 0, 1, 2
 
 
 class StackLayer(ctypes.Structure):
@@ -174,6 +175,7 @@ _SIGS = {
     "shc_stack_run": (ctypes.c_int, [_c_ptr, _c_i64, _c_ptr, STACK_FEED_FN, _c_ptr, _c_i32,
                                      _c_ptr, ctypes.POINTER(_c_i32), ctypes.POINTER(_c_i64),
                                      ctypes.POINTER(_c_i64)]),
+    "shc_stack_set_schedule": (ctypes.c_int, [_c_ptr, _c_i32]),
     "shc_stack_destroy": (ctypes.c_int, [_c_ptr]),
 }
 
@@ -665,6 +667,12 @@ class StackExecutor:
             raise err[0]
         _check(rc, "shc_stack_run")
         return int(n.value), int(cur.value), int(prev.value)
+
+    def set_schedule(self, schedule: str):
+        """shc_stack_set_schedule: "auto", "serial" or "pipelined"."""
+        code = {"auto": SHC_STACK_AUTO, "serial": SHC_STACK_SERIAL,
+                "pipelined": SHC_STACK_PIPELINED}[schedule]
+        _check(load().shc_stack_set_schedule(self._h, code), "shc_stack_set_schedule")
 
     def __del__(self):
         h = getattr(self, "_h", None)

@@ -67,6 +67,7 @@ struct Stack {
   hipEvent_t set_free[3] = {}, ready = nullptr, x_read = nullptr;
   hipEvent_t last_done[2] = {}, tail_done[2] = {}, tail_end = nullptr;
   bool busy = false;
+  int32_t schedule = SHC_STACK_AUTO;
 
   ~Stack() {
     for (hipEvent_t* e : {&set_free[0], &set_free[1], &set_free[2], &ready,
@@ -269,6 +270,7 @@ struct Stack {
   // A serial run leaves nothing on the other streams, and the next run's first
   // count arrives behind all of its work, so runs may alternate.
   bool pipeline_pays(const RunArgs& a) const {
+    if (schedule != SHC_STACK_AUTO) return schedule == SHC_STACK_PIPELINED;
     if (a.steps < 8 || d.dense_out == nullptr) return false;
     if (a.feed == nullptr) return cap() >= 300000;
     return !d.incremental && cap() * c_last * (d.dtype == SHC_BF16 ? 2 : 4) >= 200000000;
@@ -630,6 +632,20 @@ int shc_stack_run(void* stack, int64_t steps, hipStream_t stream, shc_stack_feed
   *cur_set = cur;
   *prev_rows = prev;
   return rc;
+}
+
+int shc_stack_set_schedule(void* stack, int32_t schedule) {
+  shc::clear_error();
+  if (stack == nullptr) return shc::set_error(SHC_ERR_INVALID_ARG, "stack is NULL");
+  Stack* k = static_cast<Stack*>(stack);
+  if (schedule != SHC_STACK_AUTO && schedule != SHC_STACK_SERIAL &&
+      schedule != SHC_STACK_PIPELINED)
+    return shc::set_error(SHC_ERR_INVALID_ARG, "unknown schedule %d", schedule);
+  if (schedule == SHC_STACK_PIPELINED && !k->pipelined)
+    return shc::set_error(SHC_ERR_INVALID_ARG, "a stack without side and tail streams is serial");
+  if (k->busy) return shc::set_error(SHC_ERR_INVALID_ARG, "the stack is running");
+  k->schedule = schedule;
+  return SHC_OK;
 }
 
 int shc_stack_destroy(void* stack) {

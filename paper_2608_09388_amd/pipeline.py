@@ -45,7 +45,6 @@ library's kernels.
 from __future__ import annotations
 
 import contextlib
-
 from typing import Callable, Dict, Optional, Sequence, Tuple
 
 import numpy as np

@@ -657,3 +657,4 @@ def test_stack_validation(lib):
     cur, prev, n = ctypes.c_int32(0), ctypes.c_int64(0), ctypes.c_int64(0)
     assert lib.shc_stack_run(None, 1, None, ctypes.cast(None, shc.STACK_FEED_FN), None, 0, None,
                              ctypes.byref(cur), ctypes.byref(prev), ctypes.byref(n)) == -1
+    assert lib.shc_stack_set_schedule(None, shc.SHC_STACK_SERIAL) == -1

@@ -929,6 +929,8 @@ def test_overlapped_run_new_mask_per_batch(dev, steps, side):
     xs = [synth.as_dtype(rng.standard_normal(w.x.shape).astype(np.float32), w.dtype)[1]
           for _ in range(steps)]
     st = SparseStack(w, device=str(dev), side_stream=side)
+    if side:  # (the library would run batches this few on one stream)
+        st._native.set_schedule("pipelined")
     st.run(2)                               # two index sets hold the workload's own mask
 
     def feed(k):
@@ -975,8 +977,11 @@ def test_run_under_another_stream(dev, side):
         return [o.view(torch.int16).cpu().numpy() for o in outs]
 
     ref_st = SparseStack(w, device=str(dev), side_stream=side)
-    ref = go(ref_st, torch.cuda.current_stream())
     st = SparseStack(w, device=str(dev), side_stream=side)
+    if side:
+        ref_st._native.set_schedule("pipelined")
+        st._native.set_schedule("pipelined")
+    ref = go(ref_st, torch.cuda.current_stream())
     other = torch.cuda.Stream(device=dev)
     got = go(st, other)
     for a, b in zip(got, ref):
@@ -1165,6 +1170,7 @@ def test_overlapped_run_conv_only_stack(dev, steps):
     xs = [synth.as_dtype(rng.standard_normal(w.x.shape).astype(np.float32), w.dtype)[1]
           for _ in range(steps)]
     st = SparseStack(w, device=str(dev), side_stream=True)
+    st._native.set_schedule("pipelined")
     st.run(3)
 
     def feed(k):
@@ -1194,6 +1200,7 @@ def test_overlapped_run_table_on_its_own(dev):
           for _ in range(3)]
     st = SparseStack(w, device=str(dev), side_stream=True)
     assert not st._set.fused and st._set.table_side is not None
+    st._native.set_schedule("pipelined")
     st.run(2)
 
     def feed(k):

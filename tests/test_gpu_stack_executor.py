@@ -4,7 +4,8 @@ the outputs of the same calls issued one by one from Python (pipeline.py's
 own schedules), on every workload shape the stack takes: linear-first and
 conv-first stacks, fp32 and bf16, fused and separate neighbour tables, conv
 plans, the split conv (256-channel layers), zero-fill and incremental
-scatter, pool only, serial and pipelined.
+scatter, pool only, serial and pipelined.  The pipelined cases force that
+schedule (the library would run batches this few on one stream).
 The per-call results themselves are checked against the oracle by the layer
 tests; the stack's against the oracle by test_stack_outputs_match_oracle.
 Every input is seeded and synthetic.
@@ -74,6 +75,8 @@ def run_stack(w, dev, executor, side, inc, plans, masks, batched):
                      incremental_scatter=inc, executor=executor,
                      packed_conv=False if plans else None)
     assert st.executor == executor
+    if executor == "native" and side:
+        st._native.set_schedule("pipelined")
     md = [torch.from_numpy(m).to(dev) for m in masks]
     snaps = []
 
@@ -133,6 +136,7 @@ def test_stack_outputs_match_oracle(dev):
     w = synth.workload_c4(0.05, B=24)
     masks = masks_for(w, 5)[:3]
     st = SparseStack(w, device=dev, side_stream=True, incremental_scatter=True)
+    st._native.set_schedule("pipelined")
     md = [torch.from_numpy(m).to(dev) for m in masks]
 
     def feed(k):
@@ -158,6 +162,7 @@ def test_split_conv_layers_in_stack_match_oracle(dev):
     on sampled rows at the layer bound."""
     w = synth.workload_c5(4, 8)
     st = SparseStack(w, device=dev, side_stream=True)
+    st._native.set_schedule("pipelined")
     assert sorted(st.split_rows) == [0, 1, 2]
     n = st.run(2)
     torch.cuda.synchronize()
@@ -176,6 +181,7 @@ def test_split_conv_layers_in_stack_match_oracle(dev):
 def test_native_time_events_and_feed_errors(dev):
     w = synth.workload_c4(0.05, B=8)
     st = SparseStack(w, device=dev, side_stream=True)
+    st._native.set_schedule("pipelined")
     steps = 6
     ev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
           if k % 2 == 0 else (None, None) for k in range(steps)]
@@ -198,6 +204,31 @@ def test_native_time_events_and_feed_errors(dev):
     n = st.run(2)
     torch.cuda.synchronize()
     assert n == int(np.count_nonzero(w.mask))
+
+
+def test_schedules_alternate(dev):
+    """Serial, pipelined and chosen runs of one stack in turn, each over masks of
+    its own, leave what a serial stack leaves: a run finds nothing of the run
+    before on its buffers, whichever schedule that one took.  A serial stack
+    refuses the pipelined schedule."""
+    w = synth.workload_c4(0.1, B=24)
+    st = SparseStack(w, device=dev, side_stream=True)
+    ref = SparseStack(w, device=dev)
+    with pytest.raises(shc.ShcError, match="serial"):
+        ref._native.set_schedule("pipelined")
+    rng = np.random.default_rng(12)
+    for schedule, steps in (("pipelined", 5), ("serial", 2), ("pipelined", 1), ("serial", 1),
+                            ("auto", 9), ("pipelined", 4)):
+        st._native.set_schedule(schedule)
+        masks = [torch.from_numpy((rng.random(w.B * w.V) < p).astype(np.uint8)).to(dev)
+                 for p in rng.uniform(0.0, 0.2, steps)]
+        got = []
+        for s in (st, ref):
+            n = s.run(steps, feed=lambda k: s.mask.copy_(masks[k]))
+            torch.cuda.synchronize()
+            got.append([n, s.acts[-1][:n].clone(), s.dense_out.clone(), s.pooled.clone()])
+        assert got[0][0] == got[1][0] == int(masks[-1].count_nonzero())
+        assert all(torch.equal(a, b) for a, b in zip(got[0][1:], got[1][1:])), schedule
 
 
 def test_create_refuses_plan_misuse(dev):
