@@ -44,7 +44,6 @@ library's kernels.
 """
 from __future__ import annotations
 
-import contextlib
 from typing import Callable, Dict, Optional, Sequence, Tuple
 
 import numpy as np
@@ -270,6 +269,7 @@ class SparseStack:
         # and run() order that stream after the caller's stream when they
         # are called under another one (and the caller's stream after them)
         self.main = torch.cuda.current_stream(self.device)
+        self._one_device = torch.cuda.device_count() == 1
         self._bracket = None
         # with side_stream, run() uses two more streams (default priority): the
         # side stream for the next batch's compaction and table, the tail stream
@@ -552,12 +552,15 @@ class SparseStack:
         if self._native is not None and self.side is None:
             cur = self._enter()
             try:
-                # on the stack's device, whichever is current (a switch costs
-                # the host microseconds: only where there is one)
-                here = torch.cuda.current_device() == self.main.device_index
-                with contextlib.nullcontext() if here else torch.cuda.stream(self.main):
+                # on the stack's device, whichever is current (the look and the
+                # switch cost the host microseconds: only where they matter)
+                if self._one_device or torch.cuda.current_device() == self.main.device_index:
                     n, self._cur, self.prev_n = self._native.run(
                         1, self.main, cur_set=self._cur, prev_rows=self.prev_n)
+                else:
+                    with torch.cuda.stream(self.main):
+                        n, self._cur, self.prev_n = self._native.run(
+                            1, self.main, cur_set=self._cur, prev_rows=self.prev_n)
             finally:
                 self._leave(cur)
             self._set.n = n

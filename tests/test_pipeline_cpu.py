@@ -41,7 +41,7 @@ def test_step_runs_on_the_stacks_device(monkeypatch, device):
         n = None
 
     st = pipeline.SparseStack.__new__(pipeline.SparseStack)
-    st._native, st.side, st.main = Native(), None, main
+    st._native, st.side, st.main, st._one_device = Native(), None, main, False
     st._sets, st._cur, st.prev_n = [Set(), Set()], 0, 3
     st._enter, st._leave = (lambda: None), (lambda cur: None)
     assert st.step() == 42
