@@ -334,8 +334,9 @@ int shc_sparse_neighbor_conv_table(const void* S, const int32_t* table, int64_t 
  *   slots and Cin -> Cout channels of dtype takes a plan on the current
  *   device (every smaller count does too); 0 when none does (fp32, a shape
  *   the weight-stationary kernel does not run, invalid arguments, no
- *   device).  Past it the conv runs on the tiled kernel, which builds no
- *   index lists: use shc_sparse_neighbor_conv_table there.
+ *   device).  Past it the conv runs on another kernel, which reads no plan
+ *   (the slot-major, slot-walking or tiled one): use
+ *   shc_sparse_neighbor_conv_table there.
  *
  * shc_conv_plan_bytes: bytes of a plan buffer that holds the plan of any
  *   active set of at most n_rows rows (those up to shc_conv_plan_max_rows),

@@ -196,13 +196,7 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
   const int nph = (nks + kPhaseSteps - 1) / kPhaseSteps;
   const int n0 = blockIdx.y * BN;
 
-  // workgroup b runs on XCD b % 8: each XCD takes a contiguous range of rows,
-  // so that neighbour rows of one body stay in its L2
-  const int ntiles = gridDim.x, per_xcd = ntiles / 8, rem = ntiles % 8;
-  const int xcd = blockIdx.x % 8;
-  const int tile = (xcd < rem ? xcd * (per_xcd + 1) : rem * (per_xcd + 1) + (xcd - rem) * per_xcd) +
-                   (int)(blockIdx.x / 8);
-  const int64_t row0 = (int64_t)tile * R;
+  const int64_t row0 = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * R;
   const int nrows = (int)min((int64_t)R, n - row0);
 
   // ---- weights of a phase: global -> registers -> LDS.  Rows past K Cin and

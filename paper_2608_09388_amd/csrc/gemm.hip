@@ -622,86 +622,102 @@ hipError_t launch_typed(const GemmArgs& a, hipStream_t stream) {
 
 }  // namespace
 
+// Which kernel a call takes.  "The same bits": the slot-major, weight-
+// stationary, slot-walking (but for its split fp32 products) and tiled kernels
+// sum in one order.  `plan` is filled where the weight-stationary kernel runs.
+GemmKernel gemm_kernel_of(const GemmArgs& a, bool conv, bool bf16, int cus, WsPlan* plan) {
+  const bool ws = ws_plan(a, conv, bf16, cus, plan);
+  if (!conv) return ws ? GemmKernel::kWeightStationary : GemmKernel::kTiled;
+  const int64_t per_cu = cus;  // "rows per CU" below: n_rows against a multiple of it
+  const int64_t n = a.n_rows;
+  const bool walk = conv_walk_supported(a, bf16);
+
+  // Slot-major: every output column per workgroup, the slots in turn.
+  if (conv_sm_supported(a, bf16)) {
+    // 64 -> 128 channels walks while its 128 x 32 workgroups fit one to a CU:
+    // 8.8 / 8.7 / 9.0 us at 2,000 / 4,000 / 8,000 rows against 9.6 / 9.9 / 9.9
+    if (walk && a.Cin == 64 && a.Cout == 128 && conv_walk_medium(a, cus, 1))
+      return GemmKernel::kWalk;
+    // From 1000 rows per CU, where the cost of the weight-stationary kernel's
+    // jobs (16 rows x slot) grows with the density (270,000 rows at 30%, 64 ->
+    // 64: 36 against 50 us).  Below, the density, which the host does not
+    // know, decides (nine slots, 100,000 rows, 64 -> 128: 23.2 against 20.2 us
+    // at 2%, 30 against 42 at 40%), and that kernel keeps the sparse masks.
+    // Also where its workgroups fit one to a CU (128 -> 128, 15 slots and more;
+    // 24 slots, 50,000 rows: 78 against 71 us for the slot-walking kernel,
+    // 300,000: 255 against 257).
+    if (n >= 1000 * per_cu) return GemmKernel::kSlotMajor;
+    if (conv_sm_two(a)) {
+      // where the weight-stationary kernel does not run (more than one wave of
+      // workgroups or ten slots), against the slot-walking one: nine slots,
+      // 100,000 rows at 10%, 128 -> 128 47 against 63 us; 200,000 at 5%, 64 ->
+      // 128 39 against 80, 128 -> 64 44 against 60; thirteen slots, 130,000
+      // rows, 64 -> 64 25 against 33, 128 -> 128 65 against 89
+      if (!ws && (a.Cin == 64 || n > 128 * per_cu)) return GemmKernel::kSlotMajor;
+      // 64 input channels within two 128-row workgroups per CU (nine slots: 6.6
+      // against 10.6 us at 4,200 rows, 9.5 against 13.1 at 65,000 and 2%, 64 ->
+      // 128 13.9 against 16.8; only 64 -> 64 at five slots comes near, 9.9
+      // against 12.3)
+      if (a.Cin == 64 && n <= 256 * per_cu) return GemmKernel::kSlotMajor;
+    }
+  }
+
+  // fp32 walks while its 16-row workgroups run at once: 6.9 against 16.8 us
+  // (262 rows, 16 -> 64), 12.4 against 14.5 (3,930 rows, 64 -> 64), 18.6 against
+  // 96 (1,965 rows, 128 -> 128, where W leaves no column slice and the tiled
+  // kernel ran).  Past that the weight-stationary kernel is faster at 64 input
+  // channels (17.1 against 14.9 us at 7,926 rows) and slower at few reduction
+  // entries (16 channels, 15,851 rows: 10.4 against 19.2 us; 32 channels: 12.3
+  // against 14.6), up to 32 a slot at nine slots.
+  if (walk && !bf16 &&
+      (conv_walk_small(a, cus) || (a.K * a.Cin <= 288 && conv_walk_medium(a, cus, 2))))
+    return GemmKernel::kWalk;
+
+  if (ws) return GemmKernel::kWeightStationary;
+
+  // What is left walks, but for
+  if (!walk) return GemmKernel::kTiled;  // 64-bit offsets, plans (refused there)
+  //   * short reductions into more than 64 columns from 64 rows per CU (nine
+  //     slots, 16 -> 256: 25,000 bf16 rows 15 against 20 us, 8,000 12 against 9;
+  //     200,000 fp32 rows 139 against 178; 16 -> 96: 40,000 bf16 rows 12.8
+  //     against 15.1);
+  const bool brief = a.K * a.Cin < 256;
+  if (brief && a.Cout > 64 && n > 64 * per_cu) return GemmKernel::kTiled;
+  //   * bf16 of more than 128 rows per CU with whole 128-column tiles, which the
+  //     tiled kernel gathers once where the walk gathers per 64 columns (270,000
+  //     rows, nine slots: 64 -> 256 134 against 196 us, 128 -> 256 217 against
+  //     263, 256 -> 256 388 against 401; 256 -> 64 161 against 117 the other
+  //     way, 192 -> 192 301 against 252), or with few slots to pay for the index
+  //     prologue (500,000 rows, seven slots: 48 -> 80 123 against 145 us, 32 ->
+  //     64 56 against 69; at 31,000 rows 16 against 13).
+  if (bf16 && n > 128 * per_cu && (a.Cout % 128 == 0 || a.K < 9 || brief))
+    return GemmKernel::kTiled;
+  // fp32 products are split into bf16 ones only where no other kernel runs the
+  // shape from a table either (a conv from coordinates leaves the
+  // weight-stationary kernel by density), so that a conv gives the same bits
+  // from its table and from coordinates
+  GemmArgs t = a;
+  t.table = static_cast<const int32_t*>(a.S);  // (only its presence is read)
+  WsPlan unused;
+  return ws_plan(t, conv, bf16, cus, &unused) ? GemmKernel::kWalk : GemmKernel::kWalkSplit;
+}
+
 hipError_t launch_gather_gemm(const GemmArgs& a, bool conv, bool bf16, hipStream_t stream) {
   if (a.n_rows == 0) return hipSuccess;
-  // weight-stationary kernel when a column slice of W fits in LDS
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
-  // The slot-major conv (every output column per workgroup, the slots in
-  // turn) against the weight-stationary one (column slices of W resident,
-  // jobs of 16 rows x slot), the same results bit for bit:
-  //   * where the latter does not run (more than one wave of workgroups or ten
-  //     slots): nine slots, 100,000 rows at 10%, 128 -> 128 47 against 63 us
-  //     for the slot-walking kernel; 200,000 at 5%, 64 -> 128 39 against 80,
-  //     128 -> 64 44 against 60; thirteen slots, 130,000 rows, 64 -> 64 25
-  //     against 33, 128 -> 128 65 against 89;
-  //   * from 1000 rows per CU, where the sparse jobs' cost grows with the
-  //     density (270,000 rows at 30%, 64 -> 64: 36 against 50 us).  Below, the
-  //     density, which the host does not know, decides (nine slots, 100,000
-  //     rows, 64 -> 128: 23.2 against 20.2 us at 2%, 30 against 42 at 40%), and
-  //     the weight-stationary kernel keeps the sparse masks;
-  //   * for 64 input channels also within two 128-row workgroups per CU (nine
-  //     slots: 6.6 against 10.6 us at 4,200 rows, 9.5 against 13.1 at 65,000
-  //     and 2%, 64 -> 128 13.9 against 16.8), where only 64 -> 64 at five slots
-  //     comes near (9.9 against 12.3);
-  //   * where its workgroups fit one to a CU (128 -> 128, 15 slots and more),
-  //     from 1000 rows per CU (24 slots, 50,000 rows: 78 against 71 us for the
-  //     slot-walking kernel, 300,000: 255 against 257).
-  // The slot-walking conv (conv_walk.hip) against both, the same bits:
-  //   * bf16 64 -> 128 channels: 8.8 / 8.7 / 9.0 us at 2,000 / 4,000 / 8,000
-  //     rows against 9.6 / 9.9 / 9.9 for the slot-major kernel, while its 128 x
-  //     32 workgroups fit one to a CU;
-  //   * fp32: 6.9 against 16.8 us (262 rows, 16 -> 64), 12.4 against 14.5
-  //     (3,930 rows, 64 -> 64), 18.6 against 96 (1,965 rows, 128 -> 128, where
-  //     W leaves no column slice and the tiled kernel ran) while its 16-row
-  //     workgroups run at once; past that the weight-stationary kernel is
-  //     faster at 64 input channels (17.1 against 14.9 us at 7,926 rows) and
-  //     slower at few reduction entries (16 channels, 15,851 rows: 10.4
-  //     against 19.2 us; 32 channels: 12.3 against 14.6), up to 32 a slot at
-  //     K = 9;
-  //   * what neither takes, but for sets of more than 128 rows per CU in bf16
-  //     with whole 128-column tiles, which the tiled kernel gathers once where
-  //     the walk gathers per 64 columns (270,000 rows, nine slots: 64 -> 256
-  //     134 against 196 us, 128 -> 256 217 against 263, 256 -> 256 388 against
-  //     401; 256 -> 64 161 against 117 the other way, 192 -> 192 301 against
-  //     252), or with few slots to pay for the index prologue (500,000 rows,
-  //     seven slots: 48 -> 80 123 against 145 us, 32 -> 64 56 against 69; at
-  //     31,000 rows 16 against 13); and short reductions into more than 64 columns
-  //     from 64 rows per CU (nine slots, 16 -> 256: 25,000 bf16 rows 15 against
-  //     20 us, 8,000 12 against 9; 200,000 fp32 rows 139 against 178; 16 -> 96:
-  //     40,000 bf16 rows 12.8 against 15.1).
-  const bool walk = conv && conv_walk_supported(a, bf16);
-  if (walk && bf16 && a.Cin == 64 && a.Cout == 128 && conv_sm_supported(a, bf16) &&
-      conv_walk_medium(a, cus, 1))
-    return launch_conv_walk(a, bf16, false, cus, stream);
   WsPlan plan;
-  const bool ws = ws_plan(a, conv, bf16, cus, &plan);
-  if (conv && conv_sm_supported(a, bf16) &&
-      (a.n_rows >= 1000LL * cus ||
-       (conv_sm_two(a) && (a.Cin == 64 ? a.n_rows <= 256LL * cus || !ws
-                                       : a.n_rows > 128LL * cus && !ws))))
-    return launch_conv_sm(a, cus, stream);
-  if (walk && !bf16 &&
-      (conv_walk_small(a, cus) || (a.K * a.Cin <= 288 && conv_walk_medium(a, cus, 2))))
-    return launch_conv_walk(a, bf16, false, cus, stream);
-  if (ws) return launch_ws_gemm(a, conv, bf16, plan, stream);
+  switch (gemm_kernel_of(a, conv, bf16, cus, &plan)) {
+    case GemmKernel::kSlotMajor: return launch_conv_sm(a, cus, stream);
+    case GemmKernel::kWalk: return launch_conv_walk(a, bf16, false, cus, stream);
+    case GemmKernel::kWalkSplit: return launch_conv_walk(a, bf16, true, cus, stream);
+    case GemmKernel::kWeightStationary: return launch_ws_gemm(a, conv, bf16, plan, stream);
+    case GemmKernel::kTiled: break;
+  }
   // a conv plan exists only for the weight-stationary kernel
   if (a.plan != nullptr || a.plan_out != nullptr) return hipErrorInvalidValue;
-  const bool brief = a.K * a.Cin < 256;
-  const bool tile = (brief && a.Cout > 64 && a.n_rows > 64LL * cus) ||
-                    (bf16 && a.n_rows > 128LL * cus &&
-                     (a.Cout % 128 == 0 || a.K < 9 || brief));
-  if (walk && !tile) {
-    // fp32 products split into bf16 ones only where no other kernel runs the
-    // shape from a table either (a conv from coordinates leaves the
-    // weight-stationary kernel by density), so that a conv gives the same bits
-    // from its table and from coordinates
-    GemmArgs t = a;
-    t.table = static_cast<const int32_t*>(a.S);  // (only its presence is read)
-    return launch_conv_walk(a, bf16, !ws_plan(t, conv, bf16, cus, &plan), cus, stream);
-  }
   if (bf16) return conv ? launch_typed<true, true>(a, stream) : launch_typed<true, false>(a, stream);
   return conv ? launch_typed<false, true>(a, stream) : launch_typed<false, false>(a, stream);
 }

@@ -36,7 +36,6 @@ namespace {
 
 constexpr int kGramThreads = 256;
 constexpr int kBlockThreads = 512;
-constexpr int kXcds = 8;
 constexpr int kCus = 256;
 // Rows per step of the tile kernel (both tile edges) and the workgroups of it
 // that fit on one CU: at T = 128, 240 registers per lane and 68 KB of LDS
@@ -72,9 +71,7 @@ __global__ __launch_bounds__(kGramThreads) void gram_tile_kernel(const __bf16* _
   const int tiles_side = C / T;
   const int tiles = tiles_side * tiles_side;
   const int n_wg = (int)gridDim.x;
-  const int xcd = (int)blockIdx.x % kXcds, slot = (int)blockIdx.x / kXcds;
-  const int q8 = n_wg / kXcds, r8 = n_wg % kXcds;
-  const int logical = (xcd < r8 ? xcd * (q8 + 1) : r8 * (q8 + 1) + (xcd - r8) * q8) + slot;
+  const int logical = xcd_tile(blockIdx.x, n_wg);
   const int items = n_wg / splits;
   const int split = logical / items;
   const int pt = logical - split * items;
@@ -199,9 +196,7 @@ __global__ __launch_bounds__(kBlockThreads) void gram_block_kernel(const __bf16*
   const int g = lane >> 4, l16 = lane & 15;
   const int wa = wave >> 2, wb = wave & 3;  // the wave's 128 x 64 part of the block
   const int n_wg = (int)gridDim.x;
-  const int xcd = (int)blockIdx.x % kXcds, slot = (int)blockIdx.x / kXcds;
-  const int q8 = n_wg / kXcds, r8 = n_wg % kXcds;
-  const int logical = (xcd < r8 ? xcd * (q8 + 1) : r8 * (q8 + 1) + (xcd - r8) * q8) + slot;
+  const int logical = xcd_tile(blockIdx.x, n_wg);
   const int items = n_wg / splits;
   const int split = logical / items;
   const int item = logical - split * items;
@@ -478,7 +473,7 @@ bool use_blocks(int32_t K, int32_t C) {
 }
 
 // Block path: m masks per 256-column block, nb blocks, items = block pairs;
-// one workgroup per CU (its LDS stage is 132 KB), so as many row splits as
+// one workgroup per CU (its two LDS stages are 128 KB), so as many row splits as
 // fill the CUs once.
 struct BlockPlan {
   int m, nb, items, splits, chunks;

@@ -189,6 +189,9 @@ int64_t conv_plan_max_rows(const GemmArgs& a, bool bf16, int num_cus);
 int64_t conv_plan_bytes_upto(const GemmArgs& a, bool bf16, int num_cus);
 hipError_t launch_ws_gemm(const GemmArgs& a, bool conv, bool bf16, const WsPlan& plan,
                           hipStream_t stream);
+// the kernel of a conv or linear layer (gemm.hip)
+enum class GemmKernel { kSlotMajor, kWalk, kWalkSplit, kWeightStationary, kTiled };
+GemmKernel gemm_kernel_of(const GemmArgs& a, bool conv, bool bf16, int cus, WsPlan* plan);
 // slot-walking conv for any shape whose buffers stay below 2 GiB
 // (conv_walk.hip), and whether its smallest workgroups (16 rows x 64 columns)
 // all run at once, or its middle ones (128 x 32) at per_cu to a CU
