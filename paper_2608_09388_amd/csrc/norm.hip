@@ -27,8 +27,8 @@
 // A body of up to kResident vectors per thread stays in registers, so HBM
 // sees one read and one write of every value; a larger body is streamed
 // three times (sums, deviations, output), the later passes mostly from L2,
-// kResident vectors per thread at a time (300 bodies of up to 10,475 rows x
-// 128 fp32, a tenth full: 338 us with one in flight, 221 us).
+// kStream vectors per thread at a time (300 bodies of up to 10,475 rows x
+// 128 fp32, a tenth full: 324 us with one in flight, 229 us).
 #include <algorithm>
 #include <cmath>
 #include <mutex>
@@ -40,6 +40,7 @@ namespace {
 
 constexpr int kNormThreads = 1024;
 constexpr int kResident = 16;  // vectors per thread held in registers
+constexpr int kStream = 8;     // vectors per thread in flight in a streamed body
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -119,7 +120,7 @@ __device__ __forceinline__ double lanes_sum(double v, int tx) {
 template <bool BF16>
 __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
     const i32x4* __restrict__ S, const int32_t* __restrict__ row_ptr, int64_t n_rows, int C,
-    int G, float eps, int vpr, i32x4* __restrict__ out) {
+    int G, float eps, int vpr, int long_parts, i32x4* __restrict__ out) {
   using NV = NormVec<BF16>;
   constexpr int N = NV::N;
   // part[slot][Cl]: channel partials (one slot per thread row, or per
@@ -129,11 +130,31 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
   // written, and a barrier at the start of each reduction keeps the next
   // partials from overwriting stat while it is still being read)
   extern __shared__ double smem[];
-  const int TX = blockDim.x, TY = blockDim.y;  // TX = vectors of this workgroup's range
-  const int ty = threadIdx.y;
-  const int tid = ty * TX + threadIdx.x;
-  const int Cl = TX * N;                       // channels of the range
-  const int tx = blockIdx.y * TX + threadIdx.x;  // vector within the row
+  int TX = blockDim.x, TY = blockDim.y;  // TX = vectors of this workgroup's range
+  const int tid = threadIdx.y * TX + threadIdx.x;
+
+  int64_t lo = row_ptr[blockIdx.x], hi = row_ptr[blockIdx.x + 1];
+  lo = lo < 0 ? 0 : (lo > n_rows ? n_rows : lo);
+  hi = hi < lo ? lo : (hi > n_rows ? n_rows : hi);
+  const int rows = (int)(hi - lo);
+  if (rows == 0) return;  // uniform over the workgroup
+  // long_parts > 1: a body whose whole rows do not fit this workgroup's
+  // registers is the work of all long_parts workgroups of its grid column, a
+  // channel range of whole groups each, the threads that leaves on more rows;
+  // any other body is the first one's alone
+  int lx = threadIdx.x, ty = threadIdx.y;
+  if (long_parts > 1) {
+    if (rows > TY * kResident) {
+      TX /= long_parts;
+      TY *= long_parts;
+      lx = tid % TX;
+      ty = tid / TX;
+    } else if (blockIdx.y != 0) {
+      return;
+    }
+  }
+  const int Cl = TX * N;                // channels of the range
+  const int tx = blockIdx.y * TX + lx;  // vector within the row
   // rows a wavefront holds: 64 / TX when TX divides 64 (then reduced by shuffles)
   const int rw = (TX <= 64 && 64 % TX == 0) ? 64 / TX : 1;
   const int slots = rw > 1 ? (TX * TY) / 64 : TY;
@@ -141,11 +162,6 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
   double* chan = smem + slots * Cl;   // [Cl]
   double* stat = smem;                // [Cl]: the group's mean, then 1/sqrt(var + eps)
 
-  int64_t lo = row_ptr[blockIdx.x], hi = row_ptr[blockIdx.x + 1];
-  lo = lo < 0 ? 0 : (lo > n_rows ? n_rows : lo);
-  hi = hi < lo ? lo : (hi > n_rows ? n_rows : hi);
-  const int rows = (int)(hi - lo);
-  if (rows == 0) return;  // uniform over the workgroup
   const bool resident = rows <= TY * kResident;
   const int cg = C / G;
   const double count = (double)rows * (double)cg;  // exact
@@ -161,10 +177,10 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
       for (int e = 0; e < N; ++e) acc[e] = lanes_sum(acc[e], TX);
       if (lane < TX)
 #pragma unroll
-        for (int e = 0; e < N; ++e) part[(tid >> 6) * Cl + threadIdx.x * N + e] = acc[e];
+        for (int e = 0; e < N; ++e) part[(tid >> 6) * Cl + lx * N + e] = acc[e];
     } else {
 #pragma unroll
-      for (int e = 0; e < N; ++e) part[ty * Cl + threadIdx.x * N + e] = acc[e];
+      for (int e = 0; e < N; ++e) part[ty * Cl + lx * N + e] = acc[e];
     }
     __syncthreads();
     const int nt = TX * TY;
@@ -224,12 +240,12 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
 
   i32x4 keep[kResident];
   double acc[N];
-  // streamed bodies: kResident rows of a thread (r, r + TY, ...; zeros past the
+  // streamed bodies: kStream rows of a thread (r, r + TY, ...; zeros past the
   // body) are in flight at once, so that a body the workgroup is small for
   // costs its bytes rather than a memory latency a row
   auto load_batch = [&](int r) {
 #pragma unroll
-    for (int k = 0; k < kResident; ++k) {
+    for (int k = 0; k < kStream; ++k) {
       const bool in = r + k * TY < rows;
       const i32x4 v = S[(lo + (in ? r + k * TY : 0)) * vpr + tx];
       keep[k] = in ? v : i32x4{0, 0, 0, 0};
@@ -255,10 +271,10 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
       }
     }
   } else {
-    for (int r = ty; r < rows; r += kResident * TY) {
+    for (int r = ty; r < rows; r += kStream * TY) {
       load_batch(r);
 #pragma unroll
-      for (int k = 0; k < kResident; ++k) {
+      for (int k = 0; k < kStream; ++k) {
         float f[N];
         NV::widen(keep[k], f);
 #pragma unroll
@@ -269,7 +285,7 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
   reduce(acc, false);
   double mu[N];
 #pragma unroll
-  for (int e = 0; e < N; ++e) mu[e] = stat[threadIdx.x * N + e];
+  for (int e = 0; e < N; ++e) mu[e] = stat[lx * N + e];
   // the mean as two fp32 terms (hi + lo): centred values (value - mu_hi) - mu_lo
   // err by 2^-24 of themselves, not of the mean
   float mu_hi[N], mu_lo[N];
@@ -280,9 +296,12 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
   }
 
   // ---- pass 2: squared deviations from the group mean --------------------------
-  // A thread's squares (positive terms) are summed in fp32 over four rows at a
-  // time when resident (relative error at most 3 * 2^-24), kResident rows
-  // when streamed (15 * 2^-24); the sums go on in fp64.
+  // A thread's squares (positive terms) are summed in fp32 over kSquares rows at
+  // a time, then in fp64: four for fp32 data (relative error at most 3 * 2^-24),
+  // kResident for bf16 (15 * 2^-24, against the 2^-9 of its rounded outputs;
+  // four took 185 against 172 us for 2,048 bodies of 328 rows x 256); kStream
+  // when streamed (7 * 2^-24).
+  constexpr int kSquares = BF16 ? kResident : 4;
 #pragma unroll
   for (int e = 0; e < N; ++e) acc[e] = 0.0;
   if (resident) {
@@ -301,7 +320,7 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
           sq[e] = __builtin_fmaf(d, d, sq[e]);
         }
       }
-      if (k % 4 == 3) {  // four squares at most in fp32
+      if (k % kSquares == kSquares - 1) {
 #pragma unroll
         for (int e = 0; e < N; ++e) {
           acc[e] += (double)sq[e];
@@ -310,13 +329,13 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
       }
     }
   } else {
-    for (int r0 = ty; r0 < rows; r0 += kResident * TY) {
+    for (int r0 = ty; r0 < rows; r0 += kStream * TY) {
       float sq[N];
 #pragma unroll
       for (int e = 0; e < N; ++e) sq[e] = 0.f;
       load_batch(r0);
 #pragma unroll
-      for (int k = 0; k < kResident; ++k) {
+      for (int k = 0; k < kStream; ++k) {
         float f[N];
         NV::widen(keep[k], f);
 #pragma unroll
@@ -332,7 +351,7 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
   reduce(acc, true);
   double rs[N];
 #pragma unroll
-  for (int e = 0; e < N; ++e) rs[e] = stat[threadIdx.x * N + e];
+  for (int e = 0; e < N; ++e) rs[e] = stat[lx * N + e];
 
   // ---- pass 3: normalized values -----------------------------------------------
   float rs_f[N];
@@ -350,10 +369,10 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
     for (int k = 0; k < kResident; ++k)
       if (k * TY < rows && ty + k * TY < rows) emit(keep[k], ty + k * TY);
   } else {
-    for (int r = ty; r < rows; r += kResident * TY) {
+    for (int r = ty; r < rows; r += kStream * TY) {
       load_batch(r);
 #pragma unroll
-      for (int k = 0; k < kResident; ++k)
+      for (int k = 0; k < kStream; ++k)
         if (r + k * TY < rows) emit(keep[k], r + k * TY);
     }
   }
@@ -381,13 +400,9 @@ int group_norm_split(int32_t B, int32_t C, int32_t G, int is_bf16, int num_cus) 
 // and a thread per channel in the reductions.  Several workgroups then share
 // a CU, so one's barriers and memory latency hide behind the others, and
 // short bodies leave no threads without rows.  2,048 frames of 65 rows x 256
-// fp32: 71.4 us with 1024 threads, 44.9 us with 512 (6.1 TB/s of 274 MB).  A
-// body far above the mean is streamed by few threads: 300 bodies of 655 x 128
-// fp32, a tenth of them full and the others empty, 17.4 us with 1024 threads,
-// 24.6 with 256 (42 with one row of a thread in flight); the same body alone
-// among bodies of 65 rows 17.5 and 24.5 (40.5); 2,048 frames of geometric
-// sizes x 256 bf16 103 and 49 (67).  Even 300 bodies take 15.2 and 8.8, and
-// which of the two a mask is the host does not know.
+// fp32: 68.6 us with 1024 threads, 47.0 us with 512 (5.8 TB/s of 274 MB).  A
+// body far above the mean, which the host does not see, takes its share of
+// the others' workgroups (group_norm_long_parts).
 static int group_norm_threads(int64_t n_rows, int32_t B, int32_t C, int is_bf16, int split,
                               int num_cus) {
   if ((int64_t)B * split <= num_cus) return kNormThreads;
@@ -397,6 +412,25 @@ static int group_norm_threads(int64_t n_rows, int32_t B, int32_t C, int is_bf16,
   for (int t = 256; t < kNormThreads; t *= 2)
     if (t / tx >= (is_bf16 ? 8 : 4) && (double)(t / tx) * kResident >= want) return t;
   return kNormThreads;
+}
+
+// Workgroups that share a body longer than one of them holds, where they have
+// fewer than kNormThreads threads (and a body is not split anyway): together
+// kNormThreads, while a range keeps 64 bytes of a row and whole groups.  The
+// partials need no more LDS: long_parts times the rows of 1 / long_parts of the
+// channels.  us with 1024 threads / one small workgroup, which streams the body a
+// row at a time / shared: 300 bodies of 655 rows x 128 fp32, a tenth full and the
+// others empty 17.1 / 40.5 / 13.8, the same body alone among bodies of 65 rows
+// 16.8 / 39.8 / 12.7; 2,048 frames of geometric sizes x 256 bf16 104 / 67 / 45.5.
+// Even bodies pay for the workgroups that end at once: 300 x 65 rows x 128 fp32
+// 15.1 / 8.1 / 8.4, 2,048 x 65 x 256 68.6 / 46.3 / 47.0.
+static int group_norm_long_parts(int32_t C, int32_t G, int is_bf16, int threads) {
+  const int vpr = C * (is_bf16 ? 2 : 4) / 16, cg = C / G;
+  int f = 1;
+  while (2 * f * threads <= kNormThreads && vpr % (2 * f) == 0 && vpr / (2 * f) >= 4 &&
+         (C / (2 * f)) % cg == 0)
+    f *= 2;
+  return f;
 }
 
 static size_t group_norm_lds_bytes(int32_t C, int is_bf16, int split, int threads) {
@@ -414,6 +448,7 @@ hipError_t launch_group_norm(const void* S, const int32_t* row_ptr, int64_t n_ro
   const int split = group_norm_split(B, C, G, is_bf16, num_cus);
   const int threads = B > 0 ? group_norm_threads(n_rows, B, C, is_bf16, split, num_cus)
                             : kNormThreads;
+  const int long_parts = group_norm_long_parts(C, G, is_bf16, threads);
   const dim3 block(vpr / split, threads / (vpr / split));
   const size_t lds = group_norm_lds_bytes(C, is_bf16, split, threads);
   // up to 96 KB of dynamic LDS (C = 4096 bf16): allow it once per instantiation
@@ -429,12 +464,12 @@ hipError_t launch_group_norm(const void* S, const int32_t* row_ptr, int64_t n_ro
   if (attr_err != hipSuccess) return attr_err;
   if (B <= 0 || n_rows <= 0) return hipSuccess;
   if (is_bf16)
-    hipLaunchKernelGGL(group_norm_kernel<true>, dim3(B, split), block, lds, stream,
-                       static_cast<const i32x4*>(S), row_ptr, n_rows, C, G, eps, vpr,
+    hipLaunchKernelGGL(group_norm_kernel<true>, dim3(B, split * long_parts), block, lds, stream,
+                       static_cast<const i32x4*>(S), row_ptr, n_rows, C, G, eps, vpr, long_parts,
                        static_cast<i32x4*>(out));
   else
-    hipLaunchKernelGGL(group_norm_kernel<false>, dim3(B, split), block, lds, stream,
-                       static_cast<const i32x4*>(S), row_ptr, n_rows, C, G, eps, vpr,
+    hipLaunchKernelGGL(group_norm_kernel<false>, dim3(B, split * long_parts), block, lds, stream,
+                       static_cast<const i32x4*>(S), row_ptr, n_rows, C, G, eps, vpr, long_parts,
                        static_cast<i32x4*>(out));
   return hipGetLastError();
 }

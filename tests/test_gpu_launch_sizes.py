@@ -134,6 +134,36 @@ def test_norm_streams_long_bodies(dev, dtype):
                     gn_floor(S, rp, G), "group norm of long bodies")
 
 
+# bodies longer than a small workgroup's registers hold, shared by the
+# workgroups of their grid column: 256 threads and four ranges of 16 (C 256),
+# 8 (128) and 6 vectors (96), two where groups (G 2) or 64 bytes a row (C 32)
+# allow no more, none (G 1), and 512 threads with two (mean of 65 rows); at and
+# beside the rows that one workgroup and all of them hold
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("C,G,mean", [(256, 32, 6), (128, 32, 6), (96, 4, 6), (128, 2, 6),
+                                      (32, 8, 6), (256, 1, 6), (256, 32, 65)])
+def test_norm_long_bodies_share_channels(dev, dtype, C, G, mean):
+    B = 600
+    rng = np.random.default_rng(C + G + mean)
+    rows = rng.integers(0, 2 * mean, size=B)
+    tx = C * (2 if dtype == "bf16" else 4) // 16
+    held = 16 * ((256 if mean == 6 else 512) // tx)
+    lens = [held - 1, held, held + 1, held + 17]
+    lens += [k * held + d for k in (2, 4) for d in (-1, 0, 1)]
+    at = rng.permutation(B)[:len(lens)]
+    rows[at] = lens
+    rp = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    n = int(rp[-1])
+    S = (rng.standard_normal((n, C)) * 2.0 + rng.standard_normal(C) * 3.0).astype(np.float32)
+    S = synth.as_dtype(S, dtype)[1]
+    out = torch.full((n + 3, C), float("nan"), dtype=TORCH[dtype], device=dev)
+    shc.segment_group_norm(up(S, dtype), up(rp), n, B, G, out)
+    got = down(out)
+    assert np.all(np.isnan(got[n:]))
+    assert_gn_close(got[:n], O.group_norm(S.astype(np.float64), rp, G), dtype,
+                    gn_floor(S, rp, G), f"long bodies C={C} G={G} mean={mean}")
+
+
 @pytest.mark.parametrize("V,n,K", [(40, 1, 1), (200, 63, 9), (200, 64, 9), (300, 65, 5),
                                    (655, 1300, 9)])
 def test_transposed_table_blocks(dev, V, n, K):
