@@ -278,6 +278,9 @@ int shc_gather_sparse_linear(const void* x, const int32_t* coords, int64_t n_row
  * than the fp32 matrix cores', which take every other row.  Which form a shape
  * takes follows n_rows, so the last bits of a row's result may differ between
  * calls of different n_rows; calls of the same arguments give the same bits.
+ * W is meant to be finite: kernels multiply absent rows as zeros where rows
+ * beside them have the slot, so an infinite or NaN weight may make NaN of rows
+ * that do not use it, and not the same ones in every call.
  */
 int shc_sparse_neighbor_conv(const void* S, const int32_t* coords, const int32_t* inv,
                              int64_t n_rows, int32_t B, int32_t V, const int32_t* nbr, int32_t K,

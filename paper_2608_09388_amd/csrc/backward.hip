@@ -28,9 +28,8 @@
 //   * wgrad (dW)   -- per slot, the Gram-type contraction S[r_ij]^T dZ[i] over
 //     the rows i where slot j is present.  Those rows come from a compaction
 //     of the [K][N'] table's present entries (slot-major lists, ascending i);
-//     each list
-//     is cut into chunks of a fixed number of rows, a workgroup multiplies one
-//     chunk into a fp32 partial tile, and the partials of a slot are summed in
+//     each list is cut into chunks of a fixed number of rows, a workgroup
+//     multiplies one chunk into a fp32 partial tile, and the partials of a slot are summed in
 //     chunk order in fp64.
 // Every sum has a fixed order, so results repeat bit for bit.
 #include <algorithm>

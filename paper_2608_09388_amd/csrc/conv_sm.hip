@@ -201,50 +201,8 @@ __global__ __launch_bounds__(64 * NW, MINW) void conv_sm_kernel(const SmArgs a) 
     }
   }
   __syncthreads();
-  // Rows sorted by their first sparse slot (a slot present in fewer than
-  // half the rows), so that rows sharing it share 16-row blocks and a
-  // block's slot is more often present in none of its rows: a counting sort
-  // over buckets 0 (dense slots only), 1 + j (first sparse slot j), K + 1
-  // (past the last row); the order inside a bucket is whatever the atomics
-  // give, which no result depends on (every row's sum runs over its own
-  // slots in order).
-  constexpr int RPT = (R + NT - 1) / NT;  // rows per thread
-  int bkt[RPT];
-  uint32_t dense = 0;
-  for (int j = 0; j < K; ++j) dense |= (2 * cnt[j] >= nrows ? 1u : 0u) << j;
-#pragma unroll
-  for (int i = 0; i < RPT; ++i) {
-    const int t = tid + i * NT;
-    bkt[i] = -1;
-    if (t < R) {
-      uint32_t rm = 0;
-      for (int j = 0; j < K; ++j) rm |= (srcs_in[j * R + t] >= 0 ? 1u : 0u) << j;
-      const uint32_t key = rm & ~dense;
-      bkt[i] = t >= nrows ? K + 1 : (key ? 1 + __builtin_ctz(key) : 0);
-      atomicAdd(&hist[bkt[i]], 1);
-    }
-  }
-  __syncthreads();
-  if (wave == 0) {  // exclusive scan of the K + 2 <= 34 counts, one per lane
-    const int c = lane < K + 2 ? hist[lane] : 0;
-    int inc = c;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int y = __shfl_up(inc, d, 64);
-      if (lane >= d) inc += y;
-    }
-    if (lane < K + 2) hist[lane] = inc - c;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < RPT; ++i) {
-    const int t = tid + i * NT;
-    if (t < R) {
-      const int pos = atomicAdd(&hist[bkt[i]], 1);
-      perm[pos] = t;
-      for (int j = 0; j < K; ++j) srcs[j * R + pos] = srcs_in[j * R + t];
-    }
-  }
+  // (every row's sum runs over its own slots in order, wherever it is placed)
+  sort_by_first_slot<R, NT>(K, nrows, srcs_in, cnt, hist, srcs, perm, [](int, uint32_t) {});
   __syncthreads();
   // presence of each (slot, sorted 16-row block)
   for (int e = tid; e < KR; e += NT) {
@@ -438,9 +396,10 @@ hipError_t launch_sm_k(const SmArgs& a, hipStream_t stream) {
 // 100,000 rows 47.2 against 51.2): a third fewer weight bytes from
 // L2 (each workgroup reads all of them, 32 KB a slot), which bound its sparse
 // masks (nine slots, 258,048 rows at 5% 84.2 us with 128 rows, 75.1 with 192,
-// 80.5 with one workgroup of 256 a CU; 600,000 at 50% 232, 197 and 255).  Eleven to fourteen slots 128 rows (192 leave one workgroup a
-// CU: 100,000 rows, eleven slots, 50 against 76 us), 15 and more 320 rows: one
-// wavefront per SIMD holding five blocks.
+// 80.5 with one workgroup of 256 a CU; 600,000 at 50% 232, 197 and 255).  Eleven
+// to fourteen slots take 128 rows (192 leave one workgroup a CU: 100,000 rows,
+// eleven slots, 50 against 76 us), 15 and more 320 rows: one wavefront per SIMD
+// holding five blocks.
 template <int KS, int NCT>
 hipError_t launch_sm_rows(const SmArgs& a, int num_cus, hipStream_t stream) {
   if constexpr (KS == 4) {

@@ -37,9 +37,9 @@
 // of a product (root mean square about 2^-27; the rounding of an fp32 sum is
 // up to 2^-24 of the sum).  The h h products are summed in one accumulator, the
 // others, at most 2^-7 of them, in a second; the two and the bias are added in
-// fp64 and rounded once.  So a 32-entry k-step rounds the large sum once, where the fp32 matrix
-// cores round it for each of its four-entry groups with a nonzero product, and
-// the 2-norm error against 64 bits is below theirs from dense features to two
+// fp64 and rounded once.  So a 32-entry k-step rounds the large sum once, where
+// the fp32 matrix cores round it for each of its four-entry groups with a
+// nonzero product, and the 2-norm error against 64 bits is below theirs from dense features to two
 // nonzero products an output (128 -> 128, nine slots half present, fp32 matrix
 // cores / split: dense 4.7e-7 / 1.5e-7, half of the features nonzero 3.3e-7 /
 // 1.2e-7, a tenth 1.5e-7 / 5.8e-8, 0.4% 3.9e-8 / 2.6e-8; with all six products
@@ -128,7 +128,9 @@ __device__ __forceinline__ void split3(walk_v2u32 x, uint32_t* h, uint32_t* m, u
 // other input values, and every row of a workgroup that meets other weights,
 // are computed again on the fp32 matrix cores; the rows beside them in a
 // wavefront keep their split sums (the order of rows inside a sort bucket
-// differs from launch to launch).
+// differs from launch to launch).  The second sums cost about what the fp32
+// kernel does: 498,778 rows 64 -> 64 290 us, 640 with one tiny weight or a tiny
+// value in 2% of the rows; 391 with all products on the fp32 matrix cores.
 constexpr float kSplitMin = 0x1p-100f;
 constexpr float kSplitMaxA = 0x1p96f;
 constexpr float kSplitMaxW = 0x1p24f;
@@ -314,49 +316,11 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
   }
   if constexpr (SORT) {
     __syncthreads();
-    // rows sorted by their first sparse slot (one present in fewer than half
-    // of the rows): bucket 0 has dense slots only, 1 + j first sparse slot j,
-    // K + 1 is past the last row.  The order inside a bucket is whatever the
-    // atomics give, which no result depends on: a row's sums are its own.
-    constexpr int RPT = (R + NT - 1) / NT;
-    int bkt[RPT];
-    uint32_t rm[RPT];
-    uint32_t dense = 0;
-    for (int j = 0; j < K; ++j) dense |= (2 * cnt[j] >= nrows ? 1u : 0u) << j;
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) {
-      const int t = tid + i * NT;
-      rm[i] = 0;
-      bkt[i] = -1;
-      if (t < R) {
-        for (int j = 0; j < K; ++j) rm[i] |= (srcs_in[j * R + t] >= 0 ? 1u : 0u) << j;
-        const uint32_t key = rm[i] & ~dense;
-        bkt[i] = t >= nrows ? K + 1 : (key ? 1 + __builtin_ctz(key) : 0);
-        atomicAdd(&hist[bkt[i]], 1);
-      }
-    }
-    __syncthreads();
-    if (wave == 0) {  // exclusive scan of the K + 2 <= 34 counts, one per lane
-      const int c = lane < K + 2 ? hist[lane] : 0;
-      int inc = c;
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        const int y = __shfl_up(inc, d, 64);
-        if (lane >= d) inc += y;
-      }
-      if (lane < K + 2) hist[lane] = inc - c;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) {
-      const int t = tid + i * NT;
-      if (t < R) {
-        const int pos = atomicAdd(&hist[bkt[i]], 1);
-        perm[pos] = t;
-        for (int j = 0; j < K; ++j) srcs[j * R + pos] = srcs_in[j * R + t];
-        if (rm[i]) atomicOr(&blkmask[pos >> 4], rm[i]);
-      }
-    }
+    // (a row's sums are its own, wherever it is placed)
+    sort_by_first_slot<R, NT>(K, nrows, srcs_in, cnt, hist, srcs, perm,
+                              [&](int pos, uint32_t slots) {
+                                if (slots) atomicOr(&blkmask[pos >> 4], slots);
+                              });
   }
   store_w(0, wreg[0]);
   load_w(NWS, wreg[0]);

@@ -16,8 +16,8 @@
 //
 // This file holds the tiled kernel, which runs linear layers of large shapes,
 // large bf16 convs of wide outputs or few slots, and convs whose buffers need
-// 64-bit offsets, and the dispatch over it and
-// the other conv and linear kernels (launch_gather_gemm).
+// 64-bit offsets, and the dispatch over it and the other conv and linear kernels
+// (launch_gather_gemm).
 //
 // Tiling (one workgroup = 4 wavefronts = 256 threads):
 //   * a tile of BM = 128 active rows x BN (64 or 128) output channels; tiles

@@ -43,6 +43,61 @@ __device__ __forceinline__ int xcd_tile(int b, int n) {
   return x * q + (x < r ? x : r) + (b >> 3);
 }
 
+// Rows of a workgroup sorted by their first sparse slot (a slot present in fewer
+// than half of the rows), so that rows sharing it share 16-row blocks and a
+// block's slot is more often present in none of its rows: a counting sort over
+// buckets 0 (dense slots only), 1 + j (first sparse slot j), K + 1 (past the
+// last row).  LDS: srcs_in [K][R] by row and cnt [K] (rows present per slot) are
+// read behind a barrier, hist [K + 2] is zero; srcs [K][R] by position and perm
+// [R] (position -> row) are written, placed(position, the row's slots) called
+// for every row.  The order inside a bucket is whatever the atomics give, which
+// no result may depend on.
+template <int R, int NT, typename Placed>
+__device__ __forceinline__ void sort_by_first_slot(int K, int nrows, const int32_t* srcs_in,
+                                                   const int32_t* cnt, int32_t* hist,
+                                                   int32_t* srcs, int32_t* perm, Placed&& placed) {
+  constexpr int RPT = (R + NT - 1) / NT;  // rows per thread
+  const int tid = threadIdx.x, lane = tid & 63;
+  int bkt[RPT];
+  uint32_t rm[RPT];
+  uint32_t dense = 0;
+  for (int j = 0; j < K; ++j) dense |= (2 * cnt[j] >= nrows ? 1u : 0u) << j;
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const int t = tid + i * NT;
+    rm[i] = 0;
+    bkt[i] = -1;
+    if (t < R) {
+      for (int j = 0; j < K; ++j) rm[i] |= (srcs_in[j * R + t] >= 0 ? 1u : 0u) << j;
+      const uint32_t key = rm[i] & ~dense;
+      bkt[i] = t >= nrows ? K + 1 : (key ? 1 + __builtin_ctz(key) : 0);
+      atomicAdd(&hist[bkt[i]], 1);
+    }
+  }
+  __syncthreads();
+  if (tid < 64) {  // exclusive scan of the K + 2 <= 34 counts, one per lane
+    const int c = lane < K + 2 ? hist[lane] : 0;
+    int inc = c;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int y = __shfl_up(inc, d, 64);
+      if (lane >= d) inc += y;
+    }
+    if (lane < K + 2) hist[lane] = inc - c;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const int t = tid + i * NT;
+    if (t < R) {
+      const int pos = atomicAdd(&hist[bkt[i]], 1);
+      perm[pos] = t;
+      for (int j = 0; j < K; ++j) srcs[j * R + pos] = srcs_in[j * R + t];
+      placed(pos, rm[i]);
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // launchers (host side, enqueue only; arguments already validated)
 // ---------------------------------------------------------------------------
