@@ -271,13 +271,13 @@ int shc_gather_sparse_linear(const void* x, const int32_t* coords, int64_t n_row
  *   out     [n_rows][Cout], must not overlap S.
  * n_rows = 0 is a no-op.
  * Sums are in fp32.  fp32 convs of many rows form their products from three
- * bf16 terms a value (six of the nine products of terms, the large one summed
- * apart from the others) where no weight is infinite, 2^24 or more or, unless
- * zero, under 2^-100, and for the rows whose input values are below 2^96 and,
- * unless zero, not under 2^-100; the error against exact sums is no larger
- * than the fp32 matrix cores', which take every other row.  Which form a shape
- * takes follows n_rows, so the last bits of a row's result may differ between
- * calls of different n_rows; calls of the same arguments give the same bits.
+ * bf16 terms a value, exactly the value's 24 bits (six of the nine products of
+ * terms, the large one summed apart from the others); the error against exact
+ * sums is no larger than the fp32 matrix cores', which take the rows whose sums
+ * leave that form's range (input values of 2^104 or more, weights likewise,
+ * sums of 2^80, infinities).  Which form a shape takes follows n_rows, so the
+ * last bits of a row's result may differ between calls of different n_rows;
+ * calls of the same arguments give the same bits.
  * W is meant to be finite: kernels multiply absent rows as zeros where rows
  * beside them have the slot, so an infinite or NaN weight may make NaN of rows
  * that do not use it, and not the same ones in every call.

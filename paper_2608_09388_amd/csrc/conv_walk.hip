@@ -31,22 +31,26 @@
 // fp32 in the largest workgroups takes each product as six bf16 ones (SPLIT; the
 // three-term splitting is that of Henry, Tang and Heinecke, "Leveraging the
 // bfloat16 artificial intelligence datatype for higher-precision
-// computations", 2019): an fp32 value is three bf16 terms h + m + l exactly
-// (8 + 8 + 8 significand bits), and the products h h, h m, m h, m m, h l and
-// l h are exact in fp32.  Left out are m l, l m and l l, together at most 2^-23
-// of a product (root mean square about 2^-27; the rounding of an fp32 sum is
-// up to 2^-24 of the sum).  The h h products are summed in one accumulator, the
-// others, at most 2^-7 of them, in a second; the two and the bias are added in
-// fp64 and rounded once.  So a 32-entry k-step rounds the large sum once, where
-// the fp32 matrix cores round it for each of its four-entry groups with a
-// nonzero product, and the 2-norm error against 64 bits is below theirs from dense features to two
-// nonzero products an output (128 -> 128, nine slots half present, fp32 matrix
-// cores / split: dense 4.7e-7 / 1.5e-7, half of the features nonzero 3.3e-7 /
-// 1.2e-7, a tenth 1.5e-7 / 5.8e-8, 0.4% 3.9e-8 / 2.6e-8; with all six products
-// in one accumulator the split erred by 3.9e-7, 2.7e-7 and 8.4e-8 on the last
-// three).  Six 16-bit MFMAs of 32 entries take 96 cycles, eight fp32 ones 256.
-// The rows' terms are formed in registers, the weights' as they are stored to
-// LDS (three planes).
+// computations", 2019): an fp32 value, times 2^24 so that no term is too small
+// for bf16, is three bf16 terms h + m + l exactly (8 + 8 + 8 significand bits),
+// and the products h h, h m, m h, m m, h l and l h are exact in fp32.  Left out
+// are m l, l m and l l, together at most 2^-23 of a product (root mean square
+// about 2^-27; the rounding of an fp32 sum is up to 2^-24 of the sum).  The h h
+// products are summed in one accumulator, the others, at most 2^-7 of them, in a
+// second; the two are added in fp64, scaled back, and rounded once with the bias.
+// Rows whose sums are not finite (an input of 2^104 or more, an infinity, a NaN,
+// a sum of 2^80) are summed again on the fp32 matrix cores, the rows beside them
+// in a wavefront are not (the order of rows inside a sort bucket differs from
+// launch to launch).  A 32-entry k-step rounds the large sum once, where the fp32
+// matrix cores round it for each of its four-entry groups with a nonzero
+// product, and the 2-norm error against 64 bits is below theirs from dense
+// features to two nonzero products an output (128 -> 128, nine slots half
+// present, fp32 matrix cores / split: dense 4.7e-7 / 1.5e-7, half of the features
+// nonzero 3.3e-7 / 1.2e-7, a tenth 1.5e-7 / 5.8e-8, 0.4% 3.9e-8 / 2.6e-8; with
+// all six products in one accumulator the split erred by 3.9e-7, 2.7e-7 and
+// 8.4e-8 on the last three).  Six 16-bit MFMAs of 32 entries take 96 cycles,
+// eight fp32 ones 256.  The rows' terms are formed in registers, the weights' as
+// they are stored to LDS (three planes).
 //
 // What bounds it.  Few rows: the chain of phases, each about 0.6 us (barrier,
 // LDS write to read, a dependent MFMA chain), so 16-row workgroups spread over
@@ -54,11 +58,12 @@
 // of the weight-stationary kernel, 6.9 us here; 1,965 rows 128 -> 128 fp32:
 // 96 -> 18.6 us; 1,965 rows bf16 256 -> 256: 56 -> 15.8 us).  Many rows in
 // fp32: the fp32 matrix rate held it at 370 us for 499 K rows 64 -> 64 with
-// 0.91 of the slots present (400 us in the tiled kernel); split, 295 us, bound
+// 0.91 of the slots present (396 us in the tiled kernel); split, 294 us, bound
 // by the VALU work of the split, the LDS reads of three planes and the MFMAs
-// at about equal shares, and the index prologue of every workgroup (32 K rows
-// 128 -> 128: 117, 84 and 59 us; 26 K rows 256 -> 256: 259, 222 and 175 us;
-// with all products in one accumulator 282, 58 and 161 us).
+// at about equal shares, and the index prologue of every workgroup (60% of the
+// slots present, tiled kernel / split: 498,778 rows 64 -> 64 392 / 245 us, 32,000
+// rows 128 -> 128 117 / 55, 26,200 rows 256 -> 256 352 / 207, 300,000 rows 96 ->
+// 96 668 / 391; 498,778 rows with an infinity in 2% of them 614).
 // Many rows in bf16: the weight stage per 128 rows (93 K rows, K = 5, 32 -> 80:
 // 30 -> 26 us; 19 K rows, K = 7, 48 -> 80 from coordinates: 16.2 -> 11.7 us).
 #include <mutex>
@@ -100,15 +105,19 @@ __host__ __device__ constexpr int walk_wbuf(bool bf16, bool split, int bn) {
   return (split ? 3 : 1) * kPhaseSteps * (bf16 ? 32 : 16) * walk_wrow(bf16, split, bn);
 }
 // index area (words): srcs [K][R]; sorted: srcs_in [K][R], perm [R], cnt [K],
-// hist [K + 2], w_wild; blkmask [R / 16]
+// hist [K + 2]; blkmask [R / 16]
 __host__ __device__ constexpr int walk_idx_bytes(int K, int R, bool sorted) {
-  return 4 * (K * R + R / 16 + (sorted ? K * R + R + 2 * K + 3 : 0));
+  return 4 * (K * R + R / 16 + (sorted ? K * R + R + 2 * K + 2 : 0));
 }
 
-// A pair of fp32 values as three bf16 pairs, x = h + m + l exactly: each term
-// is the nearest bf16 to what is left, 8 + 8 + 8 significand bits.
+// A pair of fp32 values times 2^24 as three bf16 pairs, 2^24 x = h + m + l
+// exactly: each term is the nearest bf16 to what is left, 8 + 8 + 8 significand
+// bits.  The last bit of the smallest fp32 number is 2^-149, so scaled every
+// nonzero term is a normal bf16 number.  Values of 2^104 and more, infinities
+// and NaN leave a term that is not finite.
+constexpr float kSplitScale = 0x1p24f;
 __device__ __forceinline__ void split3(walk_v2u32 x, uint32_t* h, uint32_t* m, uint32_t* l) {
-  const float x0 = __uint_as_float(x[0]), x1 = __uint_as_float(x[1]);
+  const float x0 = __uint_as_float(x[0]) * kSplitScale, x1 = __uint_as_float(x[1]) * kSplitScale;
   const uint32_t hh = __builtin_bit_cast(
       uint32_t, __builtin_convertvector(walk_f32x2{x0, x1}, walk_bf16x2));
   const float r0 = x0 - __uint_as_float(hh << 16), r1 = x1 - __uint_as_float(hh & 0xFFFF0000u);
@@ -120,33 +129,6 @@ __device__ __forceinline__ void split3(walk_v2u32 x, uint32_t* h, uint32_t* m, u
   *l = __builtin_bit_cast(uint32_t,
                           __builtin_convertvector(walk_f32x2{s0, s1}, walk_bf16x2));
 }
-
-// The split product is used for values that are zero or in these ranges: below
-// 2^-100 the third terms would leave bf16's range, and the upper limits keep
-// every product and partial sum of the terms finite where the fp32 product is.
-// (A NaN stays one in h and in every product, as in fp32.)  Rows that use
-// other input values, and every row of a workgroup that meets other weights,
-// are computed again on the fp32 matrix cores; the rows beside them in a
-// wavefront keep their split sums (the order of rows inside a sort bucket
-// differs from launch to launch).  The second sums cost about what the fp32
-// kernel does: 498,778 rows 64 -> 64 290 us, 640 with one tiny weight or a tiny
-// value in 2% of the rows; 391 with all products on the fp32 matrix cores.
-constexpr float kSplitMin = 0x1p-100f;
-constexpr float kSplitMaxA = 0x1p96f;
-constexpr float kSplitMaxW = 0x1p24f;
-
-// The smallest and largest magnitude of the values seen.
-struct SplitRange {
-  uint32_t small = 0xFFFFFFFFu;  // 2 |bits| - 1: a zero is the largest
-  float big = 0.f;               // (ignores a NaN)
-  __device__ __forceinline__ void see(int x) {
-    small = min(small, ((uint32_t)x << 1) - 1u);
-    big = fmaxf(big, fabsf(__int_as_float(x)));
-  }
-  __device__ __forceinline__ bool outside(float max) const {
-    return small < (__builtin_bit_cast(uint32_t, kSplitMin) << 1) - 1u || !(big < max);
-  }
-};
 
 // NA: register sets of input rows (NA - 1 phases in flight); NWS: register
 // sets of weights; MINW: wavefronts per SIMD that the registers must allow.
@@ -181,8 +163,6 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
   int32_t* perm = srcs_in + K * R;                                    // [R] position -> row
   int32_t* cnt = perm + R;                                            // [K]
   int32_t* hist = cnt + K;                                            // [K + 2]
-  // split: set once a weight outside the split's range has been staged
-  volatile int* w_wild = hist + K + 2;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -227,7 +207,6 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
   };
   auto store_w = [&](int buf, const i32x4 (&wv)[NWV]) {
     unsigned char* base = smem + buf * WBUF;
-    SplitRange seen;
 #pragma unroll
     for (int u = 0; u < NWV; ++u) {
       const int v = u * NT + tid;
@@ -241,8 +220,6 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
         uint32_t h0, m0, l0, h1, m1, l1;
         split3(x, &h0, &m0, &l0);
         split3(y, &h1, &m1, &l1);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) seen.see(wv[u][i]);
         unsigned char* p = base + k * WROW + col;
         *reinterpret_cast<walk_v2u32*>(p) = walk_v2u32{h0, h1};
         *reinterpret_cast<walk_v2u32*>(p + WPL) = walk_v2u32{m0, m1};
@@ -252,9 +229,6 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
         *reinterpret_cast<i32x4*>(base + k * WROW + col) = wv[u];
       }
     }
-    if constexpr (SPLIT) {
-      if (seen.outside(kSplitMaxW)) *w_wild = 1;
-    }
   };
   i32x4 wreg[NWS][NWV];
 #pragma unroll
@@ -262,7 +236,6 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
 
   // ---- index lists ------------------------------------------------------------
   if (tid < R / 16) blkmask[tid] = 0;
-  if (SPLIT && tid == 0) *w_wild = 0;
   if constexpr (SORT) {
     for (int q = tid; q < 2 * K + 2; q += NT) cnt[q] = 0;  // cnt and hist
   }
@@ -445,7 +418,6 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
       f.v[pl] = __builtin_bit_cast(i32x4, w);
     }
   };
-  bool wild = false;  // split: an input value outside its range was met
   auto phase = [&](int p, i32x4 (&cur)[kPhaseSteps], i32x4 (&ahead)[kPhaseSteps],
                    i32x4 (&wv)[NWV]) {
     // phase p's weights were stored before this barrier; every wavefront is
@@ -472,12 +444,6 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
     if (!live) return;
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (SPLIT) {
-      SplitRange seen;
-#pragma unroll
-      for (int ks = 0; ks < kPhaseSteps; ++ks)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) seen.see(cur[ks][i]);
-      wild = wild || seen.outside(kSplitMaxA);
       // two k-steps of 32 entries; lane group g holds entries 4g .. 4g+3 of
       // each of their two 16-entry halves
       bf16x8 at[3];
@@ -555,20 +521,27 @@ __global__ __launch_bounds__(64 * RW * CW, MINW) void conv_walk_kernel(GemmArgs 
     __builtin_amdgcn_sched_barrier(0);
   };
   if constexpr (SPLIT) {
-    // a lane's accumulators are row l16's, whose entries its four lane groups hold
-    int out_of_range = (wild ? 1 : 0) | *w_wild;
-    out_of_range |= __shfl_xor(out_of_range, 16, 64);
-    out_of_range |= __shfl_xor(out_of_range, 32, 64);
-    const bool redo = out_of_range != 0;
-    // the two sums and the bias, rounded once
+    // the two sums and the bias, rounded once; sums that are not finite (values
+    // past the split's range, or sums near fp32's largest number times 2^-48)
+    // are the fp32 matrix cores' to form
     mfma_wait();
+    bool finite = true;
 #pragma unroll
     for (int ct = 0; ct < NCT; ++ct) {
       const f32x4 b = bias_of(ct);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        acc[ct][i] = (float)((double)acc[ct][i] + (double)low[ct][i] + (double)b[i]);
+      for (int i = 0; i < 4; ++i) {
+        finite = finite && fabsf(acc[ct][i]) + fabsf(low[ct][i]) < __builtin_inff();
+        acc[ct][i] = (float)(((double)acc[ct][i] + (double)low[ct][i]) *
+                                 (1.0 / ((double)kSplitScale * kSplitScale)) +
+                             (double)b[i]);
+      }
     }
+    // row l16's columns are in its four lane groups: all of them or none
+    int out_of_range = finite ? 0 : 1;
+    out_of_range |= __shfl_xor(out_of_range, 16, 64);
+    out_of_range |= __shfl_xor(out_of_range, 32, 64);
+    const bool redo = out_of_range != 0;
     if (__ballot(redo) != 0) {
       // the wavefront's rows again on the fp32 matrix cores, straight from memory
       f32x4 kept[NCT];
@@ -673,7 +646,7 @@ hipError_t launch_walk(const GemmArgs& a, hipStream_t stream) {
 // The split's 128-row workgroups run two to a CU; 256 rows in 16 wavefronts
 // stage the weights half as often and win while one round of them covers the
 // rows (128 -> 128 at 32,000 rows 53 against 59 us; at 67,040 sparse rows 117
-// against 105).
+// against 105 the other way).
 template <bool BF16>
 hipError_t launch_walk_rows(const GemmArgs& a, bool split, int num_cus, hipStream_t stream) {
   if (conv_walk_small(a, num_cus))

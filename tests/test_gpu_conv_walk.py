@@ -204,11 +204,13 @@ def test_conv_walk_split_rows_apart(dev, n, what):
         assert torch.equal(bits(conv(T, W, coords=coords)), bits(got))
 
 
-@pytest.mark.parametrize("what", ["weight column", "input channel", "products"])
+@pytest.mark.parametrize("what", ["weight column", "input channel", "products",
+                                  "subnormal inputs", "subnormal weights"])
 def test_conv_walk_split_mixed_magnitudes(dev, what):
     """Tiny values beside ordinary ones keep their precision: a weight column of
     2^-120 among ordinary columns, an input channel of 2^-120 whose neighbours
-    meet zero weights, and products near the smallest normal number.  Against
+    meet zero weights, products near the smallest normal number, and inputs or
+    weights below it.  Against
     64 bits relative to each output's sum of absolute products: fp32 sums of
     K Cin terms err by less than K Cin 2^-24 of it, and by 2^-149 an operation
     below fp32's normal range."""
@@ -221,9 +223,14 @@ def test_conv_walk_split_mixed_magnitudes(dev, what):
         W[:, :5] = 0
         W[:, 6:] = 0
         W[:, 5] *= 2.0 ** 20
-    else:
+    elif what == "products":
         S *= 2.0 ** -60
         W *= 2.0 ** -62
+    else:
+        small, large = (S, W) if what == "subnormal inputs" else (W, S)
+        small *= 2.0 ** -132
+        large *= 2.0 ** 30
+        assert bool(((small != 0) & (small.abs() < 2.0 ** -126)).any())
     ref, scale = dense_products(S, W, table)
     err = (conv(S, W).double() - ref).abs()
     # a random walk of the roundings: 4e-7 seen, 1e-6 of the scale allowed (a
@@ -239,15 +246,15 @@ def test_conv_walk_split_mixed_magnitudes(dev, what):
 def test_conv_walk_split_error(dev, n, K, Cin, Cout, keep, with_bias):
     """The split's 2-norm error against 64 bits is no larger than the fp32
     matrix cores' on the same values, from dense features to a few nonzero ones
-    a row.  Weights times 2^40 are outside the split's range and take the fp32
+    a row.  Sums times 2^100 are outside the split's range and take the fp32
     path: the same sums, scaled exactly."""
     S, W, table, conv = split_problem(dev, n, K, Cin, Cout, n + K, keep)
     bias = torch.randn(Cout, device=dev, generator=torch.Generator(dev).manual_seed(1)) \
         if with_bias else None
     ref, _ = dense_products(S, W, table, bias)
-    big = None if bias is None else bias * 2.0 ** 40
+    big = None if bias is None else bias * 2.0 ** 100
     split = (conv(S, W, bias).double() - ref).norm() / ref.norm()
-    chain = (conv(S, W * 2.0 ** 40, big).double() * 2.0 ** -40 - ref).norm() / ref.norm()
+    chain = (conv(S, W * 2.0 ** 100, big).double() * 2.0 ** -100 - ref).norm() / ref.norm()
     print(f"n={n} K={K} {Cin}->{Cout} keep={keep} bias={with_bias}: split {split:.3e} fp32 {chain:.3e}")
     # equal roundings where a row has few products: 1% for their chance
     assert split <= 1.01 * chain, (float(split), float(chain))
