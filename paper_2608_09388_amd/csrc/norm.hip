@@ -26,9 +26,9 @@
 // v_permlane16_swap / v_permlane32_swap (VALU, no LDS traffic).
 // A body of up to kResident vectors per thread stays in registers, so HBM
 // sees one read and one write of every value; a larger body is streamed
-// three times (sums, deviations, output), the later passes mostly from L2,
-// kStream vectors per thread at a time (300 bodies of up to 10,475 rows x
-// 128 fp32, a tenth full: 324 us with one in flight, 229 us).
+// three times (sums, deviations, output), the later passes mostly from L2, with
+// more bodies than CUs kStream vectors per thread at a time (300 bodies of up to
+// 10,475 rows x 128 fp32, a tenth full: 322 us one by one, 229 us).
 #include <algorithm>
 #include <cmath>
 #include <mutex>
@@ -117,7 +117,13 @@ __device__ __forceinline__ double lanes_sum(double v, int tx) {
          __builtin_bit_cast(double, ((uint64_t)d2[1] << 32) | c[1]);
 }
 
-template <bool BF16>
+// MANY: more workgroups than CUs (launch_group_norm).  Long bodies are then
+// shared (long_parts), and streamed bodies keep kStream rows of a thread in
+// flight: a workgroup that shares its CU waits for its own loads less often.
+// One to a CU, rows one after the other are faster, the compiler's loop having
+// loads in flight at all times: one body of 10,475 rows x 64 fp32 29.7 us, 35.0 in
+// batches, 16 bodies of about 5,200 rows 19.2 and 22.1.
+template <bool BF16, bool MANY>
 __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
     const i32x4* __restrict__ S, const int32_t* __restrict__ row_ptr, int64_t n_rows, int C,
     int G, float eps, int vpr, int long_parts, i32x4* __restrict__ out) {
@@ -143,7 +149,7 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
   // channel range of whole groups each, the threads that leaves on more rows;
   // any other body is the first one's alone
   int lx = threadIdx.x, ty = threadIdx.y;
-  if (long_parts > 1) {
+  if (MANY && long_parts > 1) {
     if (rows > TY * kResident) {
       TX /= long_parts;
       TY *= long_parts;
@@ -240,9 +246,7 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
 
   i32x4 keep[kResident];
   double acc[N];
-  // streamed bodies: kStream rows of a thread (r, r + TY, ...; zeros past the
-  // body) are in flight at once, so that a body the workgroup is small for
-  // costs its bytes rather than a memory latency a row
+  // kStream rows of a thread (r, r + TY, ...; zeros past the body)
   auto load_batch = [&](int r) {
 #pragma unroll
     for (int k = 0; k < kStream; ++k) {
@@ -270,7 +274,7 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
         for (int e = 0; e < N; ++e) acc[e] += (double)f[e];
       }
     }
-  } else {
+  } else if constexpr (MANY) {
     for (int r = ty; r < rows; r += kStream * TY) {
       load_batch(r);
 #pragma unroll
@@ -280,6 +284,13 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
 #pragma unroll
         for (int e = 0; e < N; ++e) acc[e] += (double)f[e];
       }
+    }
+  } else {
+    for (int r = ty; r < rows; r += TY) {
+      float f[N];
+      NV::widen(S[(lo + r) * vpr + tx], f);
+#pragma unroll
+      for (int e = 0; e < N; ++e) acc[e] += (double)f[e];
     }
   }
   reduce(acc, false);
@@ -299,8 +310,8 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
   // A thread's squares (positive terms) are summed in fp32 over kSquares rows at
   // a time, then in fp64: four for fp32 data (relative error at most 3 * 2^-24),
   // kResident for bf16 (15 * 2^-24, against the 2^-9 of its rounded outputs;
-  // four took 185 against 172 us for 2,048 bodies of 328 rows x 256); kStream
-  // when streamed (7 * 2^-24).
+  // four took 185 against 172 us for 2,048 bodies of 328 rows x 256); a batch
+  // when streamed (kStream, or kResident rows of one at a time).
   constexpr int kSquares = BF16 ? kResident : 4;
 #pragma unroll
   for (int e = 0; e < N; ++e) acc[e] = 0.0;
@@ -328,7 +339,7 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
         }
       }
     }
-  } else {
+  } else if constexpr (MANY) {
     for (int r0 = ty; r0 < rows; r0 += kStream * TY) {
       float sq[N];
 #pragma unroll
@@ -341,6 +352,23 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
 #pragma unroll
         for (int e = 0; e < N; ++e) {
           const float d = r0 + k * TY < rows ? (f[e] - mu_hi[e]) - mu_lo[e] : 0.f;
+          sq[e] = __builtin_fmaf(d, d, sq[e]);
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < N; ++e) acc[e] += (double)sq[e];
+    }
+  } else {
+    for (int r0 = ty; r0 < rows; r0 += kResident * TY) {
+      float sq[N];
+#pragma unroll
+      for (int e = 0; e < N; ++e) sq[e] = 0.f;
+      for (int r = r0; r < rows && r < r0 + kResident * TY; r += TY) {
+        float f[N];
+        NV::widen(S[(lo + r) * vpr + tx], f);
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+          const float d = (f[e] - mu_hi[e]) - mu_lo[e];
           sq[e] = __builtin_fmaf(d, d, sq[e]);
         }
       }
@@ -368,13 +396,15 @@ __global__ __launch_bounds__(kNormThreads) void group_norm_kernel(
 #pragma unroll
     for (int k = 0; k < kResident; ++k)
       if (k * TY < rows && ty + k * TY < rows) emit(keep[k], ty + k * TY);
-  } else {
+  } else if constexpr (MANY) {
     for (int r = ty; r < rows; r += kStream * TY) {
       load_batch(r);
 #pragma unroll
       for (int k = 0; k < kStream; ++k)
         if (r + k * TY < rows) emit(keep[k], r + k * TY);
     }
+  } else {
+    for (int r = ty; r < rows; r += TY) emit(S[(lo + r) * vpr + tx], r);
   }
 }
 
@@ -444,33 +474,32 @@ static size_t group_norm_lds_bytes(int32_t C, int is_bf16, int split, int thread
 hipError_t launch_group_norm(const void* S, const int32_t* row_ptr, int64_t n_rows, int32_t B,
                              int32_t C, int32_t G, float eps, int is_bf16, void* out,
                              int num_cus, hipStream_t stream) {
+  if (B <= 0 || n_rows <= 0) return hipSuccess;
   const int vpr = C * (is_bf16 ? 2 : 4) / 16;  // <= 1024 for C <= 4096
   const int split = group_norm_split(B, C, G, is_bf16, num_cus);
-  const int threads = B > 0 ? group_norm_threads(n_rows, B, C, is_bf16, split, num_cus)
-                            : kNormThreads;
+  const int threads = group_norm_threads(n_rows, B, C, is_bf16, split, num_cus);
   const int long_parts = group_norm_long_parts(C, G, is_bf16, threads);
   const dim3 block(vpr / split, threads / (vpr / split));
   const size_t lds = group_norm_lds_bytes(C, is_bf16, split, threads);
+  const bool many = (int64_t)B * split > num_cus;
+  // [bf16][many]
+  static constexpr decltype(&group_norm_kernel<true, true>) kernels[2][2] = {
+      {group_norm_kernel<false, false>, group_norm_kernel<false, true>},
+      {group_norm_kernel<true, false>, group_norm_kernel<true, true>}};
   // up to 96 KB of dynamic LDS (C = 4096 bf16): allow it once per instantiation
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [&] {
-    attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(group_norm_kernel<true>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
-    if (attr_err == hipSuccess)
-      attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(group_norm_kernel<false>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+    for (const auto& row : kernels)
+      for (const auto k : row)
+        if (attr_err == hipSuccess)
+          attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
   });
   if (attr_err != hipSuccess) return attr_err;
-  if (B <= 0 || n_rows <= 0) return hipSuccess;
-  if (is_bf16)
-    hipLaunchKernelGGL(group_norm_kernel<true>, dim3(B, split * long_parts), block, lds, stream,
-                       static_cast<const i32x4*>(S), row_ptr, n_rows, C, G, eps, vpr, long_parts,
-                       static_cast<i32x4*>(out));
-  else
-    hipLaunchKernelGGL(group_norm_kernel<false>, dim3(B, split * long_parts), block, lds, stream,
-                       static_cast<const i32x4*>(S), row_ptr, n_rows, C, G, eps, vpr, long_parts,
-                       static_cast<i32x4*>(out));
+  hipLaunchKernelGGL(kernels[is_bf16 ? 1 : 0][many ? 1 : 0], dim3(B, split * long_parts), block,
+                     lds, stream, static_cast<const i32x4*>(S), row_ptr, n_rows, C, G, eps, vpr,
+                     long_parts, static_cast<i32x4*>(out));
   return hipGetLastError();
 }
 
