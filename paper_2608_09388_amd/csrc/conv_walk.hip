@@ -58,9 +58,9 @@
 // of the weight-stationary kernel, 6.9 us here; 1,965 rows 128 -> 128 fp32:
 // 96 -> 18.6 us; 1,965 rows bf16 256 -> 256: 56 -> 15.8 us).  Many rows in
 // fp32: the fp32 matrix rate held it at 370 us for 499 K rows 64 -> 64 with
-// 0.91 of the slots present (396 us in the tiled kernel); split, 294 us, bound
-// by the VALU work of the split, the LDS reads of three planes and the MFMAs
-// at about equal shares, and the index prologue of every workgroup (60% of the
+// 0.91 of the slots present (397 us in the tiled kernel); split, 267 to 294 us
+// from card to card, bound by the VALU work of the split, the LDS reads of three
+// planes and the MFMAs at about equal shares, and the index prologue of every workgroup (60% of the
 // slots present, tiled kernel / split: 498,778 rows 64 -> 64 392 / 245 us, 32,000
 // rows 128 -> 128 117 / 55, 26,200 rows 256 -> 256 352 / 207, 300,000 rows 96 ->
 // 96 668 / 391; 498,778 rows with an infinity in 2% of them 614).
