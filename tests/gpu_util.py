@@ -5,7 +5,7 @@ import torch
 from paper_2608_09388_amd import binding as shc
 
 # per-element tolerance relative to the abs-sum scale s = sum |a||w| + |b| of
-# each output: the benchmark spec's figures, used as they stand for fp32 and as the
+# each output: the specification's figures, used as they stand for fp32 and as the
 # ceiling of the derived bf16 bound below
 RTOL = {"f32": 1e-5, "bf16": 2e-2}
 TORCH = {"f32": torch.float32, "bf16": torch.bfloat16}
@@ -80,7 +80,7 @@ def assert_scaled_close(got, ref, scale, dtype, what="", n_terms=None):
 # error 15 * 2^-24) and in fp64 beyond, so 1/sqrt(var + eps) errs by at most
 # about 8 * 2^-24 relative.  Each output is ((x - mu_hi) - mu_lo) * rs in fp32
 # with the mean as two fp32 terms: four more roundings of 2^-24 of the output.
-# In all about 12 * 2^-24 = 7e-7 relative, under the benchmark spec's 1e-5 for
+# In all about 12 * 2^-24 = 7e-7 relative, under the specified 1e-5 for
 # fp32; bf16 adds the output's rounding: 2^-8 + 16 * 2^-24.  The absolute
 # floor covers outputs near zero, where the rounding of the fp64 mean matters:
 # a sum of n values in any order is within (n - 1) 2^-53 sum |x| of exact, so
