@@ -454,6 +454,8 @@ static int group_norm_threads(int64_t n_rows, int32_t B, int32_t C, int is_bf16,
 // 16.8 / 39.8 / 12.7; 2,048 frames of geometric sizes x 256 bf16 104 / 67 / 45.5.
 // Even bodies pay for the workgroups that end at once: 300 x 65 rows x 128 fp32
 // 15.1 / 8.1 / 8.4, 2,048 x 65 x 256 68.6 / 46.3 / 47.0.
+// They come last in the grid: among the others (eight bodies' ranges in turn)
+// they take CUs' turns, and 2,048 x 65 x 256 bf16 goes from 31 to 91 us.
 static int group_norm_long_parts(int32_t C, int32_t G, int is_bf16, int threads) {
   const int vpr = C * (is_bf16 ? 2 : 4) / 16, cg = C / G;
   int f = 1;
