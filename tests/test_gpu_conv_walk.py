@@ -82,9 +82,10 @@ def test_conv_walk_against_oracle(dev, dtype, B, V, n, K, Cin, Cout):
 @pytest.mark.parametrize("what", ["tiny rows", "huge rows", "infinite rows", "NaN rows",
                                   "huge weights", "tiny weights"])
 def test_conv_walk_value_range(dev, what):
-    """fp32 products formed from bf16 terms, on values outside their range: the
-    rows and weights there go to the fp32 matrix cores, every other row stays
-    within the fp32 bound, and infinities and NaN come out as in 64 bits."""
+    """fp32 products formed from bf16 terms, on values at the ends of fp32's
+    range: rows whose sums leave the form's own range go to the fp32 matrix
+    cores, every row stays within the fp32 bound, and infinities and NaN come
+    out as in 64 bits."""
     B, V, n, K, Cin, Cout = 40, 655, 17001, 9, 128, 128
     rng = np.random.default_rng(len(what))
     nbr = rng.integers(0, V, size=(V, K)).astype(np.int32)
@@ -182,8 +183,8 @@ def bits(t):
 @pytest.mark.parametrize("n", [17001, 33500])  # 256- and 128-row workgroups
 @pytest.mark.parametrize("what", ["infinite", "huge", "tiny"])
 def test_conv_walk_split_rows_apart(dev, n, what):
-    """Values outside the split's range change the sums of the rows that use
-    them and of no other: rows that do not have the same bits as without them,
+    """Infinite, huge (outside the split's range) and tiny values change the sums
+    of the rows that use them and of no other: rows that do not have the same bits as without them,
     in every launch and from coordinates, whichever rows share a wavefront."""
     S, W, table, conv = split_problem(dev, n, 9, 128, 128, n)
     plain = conv(S, W)
